@@ -204,11 +204,10 @@ __global__ void __launch_bounds__(1024) k_chol_inv(const cd *__restrict__ G, int
 // Five stages on the stream:
 //   reduction  A = Q T Q^H, T real tridiagonal (lower Householder):
 //              k_hetrd_la (1 workgroup, n <= 192) or k_trd_apply + k_trd_step
-//   k_stebz_w / k_stebz (k groups)  lowest k eigenvalues of T by 512-point multisection
-//   k_stein_w  (k waves)       eigenvectors of T by inverse iteration, in registers (n <= 256)
-//   k_stein    (k/E groups)    the same with the LU in LDS (n > 256)
-//   k_orth_chol2 / k_orth_chol / k_orth (1 workgroup)  re-orthogonalisation
-//   k_unmtr_w / k_unmtr (k/cw groups)  back-transform V = Q Z
+//   k_stebz    (k groups)      lowest k eigenvalues of T by 256-point multisection
+//   k_stein_w  (k waves)       eigenvectors of T by inverse iteration, in registers
+//   k_orth_chol2 / k_orth_chol / k_orth (1 workgroup), k_orth_clusters  re-orthogonalisation
+//   k_unmtr_w  (k waves)       back-transform V = Q Z
 //
 // ---- multi-workgroup reduction for n > 192 (the final Rayleigh-Ritz) --------
 // H_j = I - tau_j v_j v_j^H, A <- H_j^H A H_j, w = tau y - (|tau|^2 / 2)
@@ -692,322 +691,163 @@ __global__ void __launch_bounds__(1024)
     }
 }
 
-// Sturm counts (number of eigenvalues below x) at two shifts at once: the two
-// recurrences are independent, so their division chains overlap.
-__device__ void sturm_count2(const double *d, const double *e2, int n, double x1, double x2,
-                             double pivmin, int &c1, int &c2) {
-    c1 = c2 = 0;
-    double q1 = d[0] - x1, q2 = d[0] - x2;
-    if (fabs(q1) < pivmin) q1 = -pivmin;
-    if (fabs(q2) < pivmin) q2 = -pivmin;
-    c1 += q1 < 0;
-    c2 += q2 < 0;
-    for (int i = 1; i < n; ++i) {
-        // e^2 / q by the refined hardware reciprocal (within an ulp, as the
-        // count's backward-error argument needs; |q| >= pivmin keeps it finite)
-        const double di = d[i], ei = e2[i - 1];
-        q1 = di - x1 - ei * rcp_nr(q1);
-        q2 = di - x2 - ei * rcp_nr(q2);
-        if (fabs(q1) < pivmin) q1 = -pivmin;
-        if (fabs(q2) < pivmin) q2 = -pivmin;
-        c1 += q1 < 0;
-        c2 += q2 < 0;
-    }
-}
-
 struct TriBounds {
     double gl, gu, pivmin, tnorm;
 };
 
-__device__ TriBounds tri_bounds(const double *ds, const double *ee, int n) {
-    double gl = ds[0], gu = ds[0], tnorm = 0.0;
-    for (int i = 0; i < n; ++i) {
-        const double r = (i > 0 ? fabs(ee[i - 1]) : 0.0) + (i + 1 < n ? fabs(ee[i]) : 0.0);
-        gl = fmin(gl, ds[i] - r);
-        gu = fmax(gu, ds[i] + r);
-        tnorm = fmax(tnorm, fabs(ds[i]) + r);
-    }
-    const double pivmin = DBL_MIN * fmax(1.0, tnorm * tnorm);
-    const double span = fmax(gu - gl, DBL_EPSILON * fmax(1.0, tnorm));
-    return {gl - 2.0 * DBL_EPSILON * span - 1e-300, gu + 2.0 * DBL_EPSILON * span + 1e-300, pivmin,
-            tnorm};
-}
-
-// One workgroup of 256 threads per eigenvalue: each round evaluates 512
-// interior points of the bracket (two interleaved Sturm chains per thread)
-// and keeps the sub-interval where the count crosses the index, so a bracket
-// shrinks by 513x (9 bits) per round, ~6-7 rounds from the Gershgorin
-// interval to double precision.  The first point with count > idx is found
-// by per-wave ballots and a minimum over the waves in LDS.
-constexpr int kStebzThreads = 256;
-__global__ void __launch_bounds__(kStebzThreads) k_stebz(const double *__restrict__ dd,
-                                                          const double *__restrict__ ee, int n, int /*k*/,
-                                                          double *__restrict__ w) {
-    extern __shared__ unsigned char smem_raw[];
-    double *ds = reinterpret_cast<double *>(smem_raw);
-    double *e2 = ds + n;
-    __shared__ TriBounds tb;
-    __shared__ int wfirst[2][kStebzThreads / 64];
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    constexpr int NP = 2 * kStebzThreads;   // interior points per round
-    for (int i = t; i < n; i += blockDim.x) {
-        ds[i] = dd[i];
-        e2[i] = (i + 1 < n) ? ee[i] * ee[i] : 0.0;
-    }
-    if (t == 0) tb = tri_bounds(dd, ee, n);
-    __syncthreads();
-    const int idx = blockIdx.x;
-    double lo = tb.gl, hi = tb.gu;
-    for (int round = 0; round < 16; ++round) {
-        const double width = hi - lo;
-        if (width <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + tb.pivmin) break;
-        // thread t evaluates points t and t + 256 (1-based: point p at lo + width p / (NP + 1))
-        const double x1 = lo + width * (double)(t + 1) / (double)(NP + 1);
-        const double x2 = lo + width * (double)(t + 1 + kStebzThreads) / (double)(NP + 1);
-        int c1, c2;
-        sturm_count2(ds, e2, n, x1, x2, tb.pivmin, c1, c2);
-        const uint64_t b1 = __ballot(c1 > idx), b2 = __ballot(c2 > idx);
-        const int buf = round & 1;
-        if (lane == 0) {
-            wfirst[buf][wave] = b1 ? 64 * wave + __ffsll((unsigned long long)b1) - 1
-                                   : (b2 ? kStebzThreads + 64 * wave + __ffsll((unsigned long long)b2) - 1
-                                         : NP);
-        }
-        __syncthreads();
-        // the first point (0-based) whose count exceeds idx; NP if none
-        int first = NP;
-        for (int q = 0; q < kStebzThreads / 64; ++q) {
-            const int f = wfirst[buf][q];
-            // points of the first half (< 256) come before every point of the second half
-            first = min(first, f);
-        }
-        const double nlo = first == 0 ? lo : lo + width * (double)first / (double)(NP + 1);
-        const double nhi = first == NP ? hi : lo + width * (double)(first + 1) / (double)(NP + 1);
-        lo = nlo;
-        hi = nhi;
-    }
-    if (t == 0) w[idx] = 0.5 * (lo + hi);
-}
-
-// The same multisection with d_i and e_{i-1}^2 held in registers of every wave
-// (entry i in lane i % 64, slot i / 64) and read with readlane, so the Sturm
-// chains never wait on LDS; the bounds come from wave reductions (min / max,
-// exact in any order).  Same points, counts and rounds as k_stebz.  n <= 64 RPL.
-// rel_tol: relative width at which a bracket stops (DBL_EPSILON; FLT_EPSILON
-// for a tridiagonal matrix from the FP32 reduction, whose eigenvalues carry
-// FP32 rounding anyway: 3 rounds instead of 6)
-template <int RPL>
-__global__ void __launch_bounds__(kStebzThreads) k_stebz_w(const double *__restrict__ dd,
-                                                           const double *__restrict__ ee, int n, int /*k*/,
-                                                           double *__restrict__ w, double rel_tol) {
-    __shared__ int wfirst[2][kStebzThreads / 64];
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    constexpr int NP = 2 * kStebzThreads;
-    double dreg[RPL], e2reg[RPL];
+// Gershgorin interval, pivot floor and norm of the tridiagonal matrix, by the
+// whole workgroup (min and max: exact in any order).  red: 3 doubles per wave.
+__device__ TriBounds tri_bounds(const double *__restrict__ dd, const double *__restrict__ ee, int n, double *red) {
     double gl = DBL_MAX, gu = -DBL_MAX, tnorm = 0.0;
-#pragma unroll
-    for (int q = 0; q < RPL; ++q) {
-        const int i = lane + 64 * q;
-        dreg[q] = i < n ? dd[i] : 0.0;
-        e2reg[q] = (i >= 1 && i < n) ? ee[i - 1] * ee[i - 1] : 0.0;
-        if (i < n) {
-            const double r = (i > 0 ? fabs(ee[i - 1]) : 0.0) + (i + 1 < n ? fabs(ee[i]) : 0.0);
-            gl = fmin(gl, dd[i] - r);
-            gu = fmax(gu, dd[i] + r);
-            tnorm = fmax(tnorm, fabs(dd[i]) + r);
-        }
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const double r = (i > 0 ? fabs(ee[i - 1]) : 0.0) + (i + 1 < n ? fabs(ee[i]) : 0.0);
+        gl = fmin(gl, dd[i] - r);
+        gu = fmax(gu, dd[i] + r);
+        tnorm = fmax(tnorm, fabs(dd[i]) + r);
     }
     for (int off = 32; off > 0; off >>= 1) {
         gl = fmin(gl, __shfl_xor(gl, off));
         gu = fmax(gu, __shfl_xor(gu, off));
         tnorm = fmax(tnorm, __shfl_xor(tnorm, off));
     }
-    const double pivmin = DBL_MIN * fmax(1.0, tnorm * tnorm);
-    {
-        const double span = fmax(gu - gl, DBL_EPSILON * fmax(1.0, tnorm));
-        gl = gl - 2.0 * DBL_EPSILON * span - 1e-300;
-        gu = gu + 2.0 * DBL_EPSILON * span + 1e-300;
+    const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        red[3 * wave] = gl;
+        red[3 * wave + 1] = gu;
+        red[3 * wave + 2] = tnorm;
     }
+    __syncthreads();
+    for (int q = 0; q < nw; ++q) {
+        gl = fmin(gl, red[3 * q]);
+        gu = fmax(gu, red[3 * q + 1]);
+        tnorm = fmax(tnorm, red[3 * q + 2]);
+    }
+    const double pivmin = DBL_MIN * fmax(1.0, tnorm * tnorm);
+    const double span = fmax(gu - gl, DBL_EPSILON * fmax(1.0, tnorm));
+    return {gl - 2.0 * DBL_EPSILON * span - 1e-300, gu + 2.0 * DBL_EPSILON * span + 1e-300, pivmin, tnorm};
+}
+
+// Number of eigenvalues below x from the ratios q_i = d_i - x - e_{i-1}^2 /
+// q_{i-1}: needs no scaling, but every step waits on a refined reciprocal.
+// de[i] = (d_i, e_{i-1}^2).
+__device__ int sturm_ratio(const double2 *de, int n, double x, double pivmin) {
+    double q = de[0].x - x;
+    if (fabs(q) < pivmin) q = -pivmin;
+    int c = q < 0;
+    for (int i = 1; i < n; ++i) {
+        // the hardware reciprocal refined to an ulp, as the count's
+        // backward-error argument needs; |q| >= pivmin keeps it finite
+        q = de[i].x - x - de[i].y * rcp_nr(q);
+        if (fabs(q) < pivmin) q = -pivmin;
+        c += q < 0;
+    }
+    return c;
+}
+
+// The same count as the sign changes of the leading principal minors
+//   p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2},
+// one dependent FMA per step instead of a reciprocal chain.  A computed p_i is
+// the exact one for d_i - x and e_{i-1}^2 changed by a few ulps, as in the
+// ratio form.  The entries are scaled by a power of two to norm <= 1, so |p|
+// grows at most 3x per step; every 16 steps the pair (p_i, p_{i-1}) is scaled
+// back to about 1.  A zero p_i needs no care (the next minor is then
+// -e^2 p_{i-1} and the pair counts one change in either sign of zero), but a
+// pair that has all but vanished (a split matrix with an eigenvalue at x) sets
+// `lost`, and the caller counts by ratios.
+__device__ int sturm_minors(const double2 *de, int n, double x, bool &lost) {
+    double p0 = 1.0, p1 = de[0].x - x;
+    int c = (unsigned)__double2hiint(p1) >> 31;
+    auto step = [&](int i) {
+        const double2 v = de[i];
+        const double p = fma(v.x - x, p1, -(v.y * p0));
+        c += (unsigned)(__double2hiint(p) ^ __double2hiint(p1)) >> 31;
+        p0 = p1;
+        p1 = p;
+    };
+    lost = false;
+    int i = 1;
+    for (; i + 16 <= n; i += 16) {
+#pragma unroll
+        for (int u = 0; u < 16; ++u) step(i + u);
+        const double m = fmax(fabs(p0), fabs(p1));
+        lost |= !(m > 0x1p-900);
+        const int ex = -__builtin_amdgcn_frexp_exp(m);
+        p0 = __builtin_amdgcn_ldexp(p0, ex);
+        p1 = __builtin_amdgcn_ldexp(p1, ex);
+    }
+    for (; i < n; ++i) step(i);
+    lost |= !(fmax(fabs(p0), fabs(p1)) > 0x1p-900);
+    return c;
+}
+
+// Lowest k eigenvalues, one workgroup of 256 threads per eigenvalue: each
+// round counts at 256 interior points of the bracket (one per thread) and keeps
+// the sub-interval where the count crosses the index: 8 bits a round, 7
+// rounds from the Gershgorin interval to double precision.  The first point
+// with count > idx is found by per-wave ballots and a minimum over the waves.
+// Bound by the chain of n dependent steps per round; the minors take one FMA
+// there, so one point per thread and one wave per SIMD (more points per round
+// save fewer rounds than their issue slots cost).  Lowest 64 of n = 192:
+// 133 us with the ratio form at 512 points, 36 us with the minors; all of
+// n = 512: 532 -> 117 us us.
+// rel_tol: relative width at which a bracket stops (DBL_EPSILON; FLT_EPSILON
+// for a tridiagonal matrix from the FP32 reduction, whose eigenvalues carry
+// FP32 rounding anyway).
+constexpr int kStebzThreads = 256;
+__global__ void __launch_bounds__(kStebzThreads) k_stebz(const double *__restrict__ dd,
+                                                          const double *__restrict__ ee, int n,
+                                                          double *__restrict__ w, double rel_tol,
+                                                          int *__restrict__ status) {
+    extern __shared__ double2 de[];   // [n] (d_i, e_{i-1}^2), scaled
+    __shared__ double red[3 * kStebzThreads / 64];
+    __shared__ int wfirst[2][kStebzThreads / 64];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    constexpr int NP = kStebzThreads;   // interior points per round
+    const TriBounds tb = tri_bounds(dd, ee, n, red);
+    // exact scaling to norm <= 1 (none for a zero or non-finite norm)
+    const int ex = (tb.tnorm > 0.0 && tb.tnorm <= DBL_MAX) ? __builtin_amdgcn_frexp_exp(tb.tnorm) : 0;
+    for (int i = t; i < n; i += kStebzThreads) {
+        const double e = i > 0 ? __builtin_amdgcn_ldexp(ee[i - 1], -ex) : 0.0;
+        de[i] = double2{__builtin_amdgcn_ldexp(dd[i], -ex), e * e};
+    }
+    __syncthreads();
     const int idx = blockIdx.x;
-    double lo = gl, hi = gu;
-    for (int round = 0; round < 16; ++round) {
+    double lo = tb.gl, hi = tb.gu;
+    for (int round = 0; round < 18; ++round) {
         const double width = hi - lo;
-        if (width <= 2.0 * rel_tol * fmax(fabs(lo), fabs(hi)) + pivmin) break;
-        const double x1 = lo + width * (double)(t + 1) / (double)(NP + 1);
-        const double x2 = lo + width * (double)(t + 1 + kStebzThreads) / (double)(NP + 1);
-        // Sturm counts at x1 and x2 (the recurrence of sturm_count2)
-        int c1 = 0, c2 = 0;
-        double q1 = lane_read(dreg[0], 0) - x1, q2 = lane_read(dreg[0], 0) - x2;
-        if (fabs(q1) < pivmin) q1 = -pivmin;
-        if (fabs(q2) < pivmin) q2 = -pivmin;
-        c1 += q1 < 0;
-        c2 += q2 < 0;
-        unroll_for<0, RPL>([&](auto q_) {
-            constexpr int q = q_;
-            const int lim = min(64, n - 64 * q);
-            for (int l = q == 0 ? 1 : 0; l < lim; ++l) {
-                const double di = lane_read(dreg[q], l), ei = lane_read(e2reg[q], l);
-                q1 = di - x1 - ei * rcp_nr(q1);
-                q2 = di - x2 - ei * rcp_nr(q2);
-                if (fabs(q1) < pivmin) q1 = -pivmin;
-                if (fabs(q2) < pivmin) q2 = -pivmin;
-                c1 += q1 < 0;
-                c2 += q2 < 0;
-            }
-        });
-        const uint64_t b1 = __ballot(c1 > idx), b2 = __ballot(c2 > idx);
+        if (width <= 2.0 * rel_tol * fmax(fabs(lo), fabs(hi)) + tb.pivmin) break;
+        // thread t counts at point t + 1 (point p at lo + width p / (NP + 1))
+        const double x = __builtin_amdgcn_ldexp(lo + width * (double)(t + 1) / (double)(NP + 1), -ex);
+        bool lost;
+        int c = sturm_minors(de, n, x, lost);
+        if (__any(lost)) c = sturm_ratio(de, n, x, DBL_MIN);   // uniform per wave
+        const uint64_t b = __ballot(c > idx);
         const int buf = round & 1;
-        if (lane == 0) {
-            wfirst[buf][wave] = b1 ? 64 * wave + __ffsll((unsigned long long)b1) - 1
-                                   : (b2 ? kStebzThreads + 64 * wave + __ffsll((unsigned long long)b2) - 1
-                                         : NP);
-        }
+        if (lane == 0) wfirst[buf][wave] = b ? 64 * wave + __ffsll((unsigned long long)b) - 1 : NP;
         __syncthreads();
-        int first = NP;
+        int first = NP;   // the first point (0-based) whose count exceeds idx; NP if none
+#pragma unroll
         for (int q = 0; q < kStebzThreads / 64; ++q) first = min(first, wfirst[buf][q]);
         const double nlo = first == 0 ? lo : lo + width * (double)first / (double)(NP + 1);
         const double nhi = first == NP ? hi : lo + width * (double)(first + 1) / (double)(NP + 1);
         lo = nlo;
         hi = nhi;
     }
-    if (t == 0) w[idx] = 0.5 * (lo + hi);
-}
-
-// Inverse iteration: one thread per eigenvalue, E eigenvalues per workgroup,
-// the LU factors of T - lambda I and the iterate in LDS, interleaved [i][e].
-__global__ void __launch_bounds__(64) k_stein(const double *__restrict__ dd,
-                                              const double *__restrict__ ee, int n, int k, int E,
-                                              const double *__restrict__ w, double *__restrict__ Z) {
-    extern __shared__ unsigned char smem_raw[];
-    double *ds = reinterpret_cast<double *>(smem_raw);   // [n]
-    double *es = ds + n;                                  // [n]
-    double *lu = es + n;                                  // [6][n][E]
-    __shared__ double s_tnorm;
-    const int t = threadIdx.x;
-    for (int i = t; i < n; i += blockDim.x) {
-        ds[i] = dd[i];
-        es[i] = (i + 1 < n) ? ee[i] : 0.0;
+    if (t == 0) {
+        const double v = 0.5 * (lo + hi);
+        w[idx] = v;
+        if (!isfinite(v)) atomicOr(status, 4);
     }
-    if (t == 0) s_tnorm = tri_bounds(dd, ee, n).tnorm;
-    __syncthreads();
-    const int idx = blockIdx.x * E + t;
-    if (t >= E || idx >= k) return;
-    auto at = [&](int arr, int i) -> double & { return lu[((size_t)arr * n + i) * E + t]; };
-    enum { DL = 0, DD, DU, DU2, PIV, ZZ };
-    const double lam = w[idx];
-    const double eps_t = DBL_EPSILON * fmax(s_tnorm, 1e-300);
-    // LU with partial pivoting of T - lambda I (LAPACK dlagtf order).  The
-    // entries that the next step modifies (diagonal d and superdiagonal u of
-    // row i) are carried in registers and the untouched inputs of step i + 1
-    // are loaded during step i, so the serial chain never waits on LDS.  DD
-    // keeps the reciprocal pivot, the same refined reciprocal that forms the
-    // multiplier.
-    double d_cur = ds[0] - lam, u_cur = es[0];
-    double sub = es[0];
-    double d_nx = n > 1 ? ds[1] - lam : 0.0, u_nx = n > 1 ? es[1] : 0.0;
-    for (int i = 0; i + 1 < n; ++i) {
-        const double sub_n = es[i + 1];   // es holds n entries, the last one zero
-        const double d_nx_n = i + 2 < n ? ds[i + 2] - lam : 0.0;
-        const double u_nx_n = i + 2 < n ? es[i + 2] : 0.0;
-        if (fabs(d_cur) >= fabs(sub)) {
-            const double dp = fabs(d_cur) < eps_t ? (d_cur < 0 ? -eps_t : eps_t) : d_cur;
-            const double r = rcp_nr(dp);
-            const double m = sub * r;
-            at(DD, i) = r;
-            at(DL, i) = m;
-            at(DU, i) = u_cur;
-            at(DU2, i) = 0.0;
-            at(PIV, i) = 0.0;
-            d_cur = d_nx - m * u_cur;
-            u_cur = u_nx;
-        } else {
-            const double r = rcp_nr(sub);
-            const double m = d_cur * r;
-            at(DD, i) = r;
-            at(DL, i) = m;
-            at(DU, i) = d_nx;
-            at(PIV, i) = 1.0;
-            at(DU2, i) = i + 2 < n ? u_nx : 0.0;
-            d_cur = u_cur - m * d_nx;
-            u_cur = i + 2 < n ? -m * u_nx : u_nx;
-        }
-        sub = sub_n;
-        d_nx = d_nx_n;
-        u_nx = u_nx_n;
-    }
-    at(DD, n - 1) = 1.0 / (fabs(d_cur) < eps_t ? eps_t : d_cur);
-    at(DU, n - 1) = 0.0;
-    at(DU2, n - 1) = 0.0;
-    at(PIV, n - 1) = 0.0;
-    for (int i = 0; i < n; ++i) {
-        uint64_t h = (uint64_t)(i + 1) * 0x9E3779B97F4A7C15ull ^ (uint64_t)(idx + 7) * 0xD1B54A32D192ED03ull;
-        h ^= h >> 31;
-        h *= 0xBF58476D1CE4E5B9ull;
-        h ^= h >> 29;
-        at(ZZ, i) = (double)(h >> 11) * (2.0 / 9007199254740992.0) - 1.0;
-    }
-    // two solves; the iterate stays unscaled in LDS and the 1 / max-norm of the
-    // first solve is applied as the second one reads it; inputs of the next
-    // step are again loaded one step ahead
-    double scale = 1.0, n2 = 0.0;
-    for (int iter = 0; iter < 2; ++iter) {
-        // L solve with the row interchanges; z carries the running entry
-        double z = at(ZZ, 0) * scale;
-        double znx = n > 1 ? at(ZZ, 1) * scale : 0.0, l = at(DL, 0), piv = at(PIV, 0);
-        for (int i = 0; i + 1 < n; ++i) {
-            const double znx_n = i + 2 < n ? at(ZZ, i + 2) * scale : 0.0;   // not yet overwritten
-            const double l_n = at(DL, i + 1), piv_n = at(PIV, i + 1);
-            if (piv != 0.0) {
-                at(ZZ, i) = znx;
-                z = z - l * znx;
-            } else {
-                at(ZZ, i) = z;
-                z = znx - l * z;
-            }
-            znx = znx_n;
-            l = l_n;
-            piv = piv_n;
-        }
-        at(ZZ, n - 1) = z;
-        // U solve from the bottom; z1, z2 carry the two entries below
-        double nrm = 0.0, z1 = 0.0, z2 = 0.0;
-        n2 = 0.0;
-        double zz = at(ZZ, n - 1), du = at(DU, n - 1), du2 = at(DU2, n - 1), rd = at(DD, n - 1);
-        for (int i = n - 1; i >= 0; --i) {
-            double zz_n = 0.0, du_n = 0.0, du2_n = 0.0, rd_n = 0.0;
-            if (i > 0) {   // row i - 1: L-solve output, not yet overwritten
-                zz_n = at(ZZ, i - 1);
-                du_n = at(DU, i - 1);
-                du2_n = at(DU2, i - 1);
-                rd_n = at(DD, i - 1);
-            }
-            const double sv = (zz - du * z1 - du2 * z2) * rd;
-            at(ZZ, i) = sv;
-            nrm = fmax(nrm, fabs(sv));
-            n2 += sv * sv;
-            z2 = z1;
-            z1 = sv;
-            zz = zz_n;
-            du = du_n;
-            du2 = du2_n;
-            rd = rd_n;
-        }
-        scale = nrm > 0 ? 1.0 / nrm : 1.0;
-    }
-    // unit 2-norm (the second solve's result is at most ~1 / eps_t in size,
-    // so its squares stay far from overflow)
-    const double inv = n2 > 0 ? 1.0 / sqrt(n2) : 1.0;
-    for (int i = 0; i < n; ++i) Z[(int64_t)i * k + idx] = at(ZZ, i) * inv;
 }
 
 // Inverse iteration, one eigenvalue per wave, with no memory access inside the
 // recurrences: every lane runs the same (wave-uniform) LU factorisation and
 // solves, entry i of each per-step array (the LU factors, the iterate, d and e)
 // is kept by lane i % 64 in register slot i / 64, written with a lane select and
-// read back with readlane.  The arithmetic and its order are those of k_stein
-// (LU with partial pivoting of T - lambda I in dlagtf order, two solves from a
-// hashed start vector, unit 2-norm), with the pivot choice taken by selects.
-// n <= 64 RPL.
+// read back with readlane.  LU with partial pivoting of T - lambda I (dlagtf
+// order, the pivot choice taken by selects), two solves from a hashed start
+// vector, unit 2-norm.  n <= 64 RPL; all of n = 512: 237 us (385 us with the
+// factors in LDS and up to four eigenvalues in a workgroup).
 template <int RPL>
 __global__ void __launch_bounds__(64) k_stein_w(const double *__restrict__ dd,
                                                 const double *__restrict__ ee, int n, int k,
@@ -1142,63 +982,73 @@ __global__ void __launch_bounds__(64) k_stein_w(const double *__restrict__ dd,
     }
 }
 
-// Gram-Schmidt (twice) of the columns of Z [n][k] in eigenvalue order.  In
-// LDS when it fits; otherwise only within clusters of eigenvalues closer than
-// ctol (vectors of separated eigenvalues are already orthogonal to ~n eps ||T|| / gap,
-// the backward error of the inverse-iteration solves over the gap).
-__global__ void __launch_bounds__(1024) k_orth(double *__restrict__ Zg, int n, int k, int in_lds,
-                                               const double *__restrict__ w, double ctol_rel,
-                                               const double *__restrict__ dd,
-                                               const double *__restrict__ ee) {
-    extern __shared__ unsigned char smem_raw[];
-    double *coef = reinterpret_cast<double *>(smem_raw);   // [k]
-    double *red = coef + k;                                 // [blockDim]
-    double *Zl = red + blockDim.x;                          // [n][k] if in_lds
+// Gram-Schmidt (twice) of column j of Z [rows r, leading dimension ldz] against
+// columns [i0, j), with normalisation after each pass, by the whole workgroup.
+// coef: [j - i0] doubles, red: one double per wave.
+__device__ void gs_column(double *Z, int64_t ldz, int n, int i0, int j, double *coef, double *red) {
     const int t = threadIdx.x, nt = blockDim.x, lane = t & 63, wave = t >> 6, nw = nt >> 6;
-    const int ldz = in_lds ? k + 1 : k;   // padded rows in LDS (no bank conflicts)
-    double *Z = in_lds ? Zl : Zg;
-    __shared__ double s_ctol;
-    if (t == 0) s_ctol = ctol_rel * fmax(tri_bounds(dd, ee, n).tnorm, 1e-300);
-    __syncthreads();
-    const double ctol = s_ctol;
-    if (in_lds) {
-        for (int i = t; i < n * k; i += nt) Zl[(i / k) * ldz + i % k] = Zg[i];
-        __syncthreads();
-    }
-    int cstart = 0;
-    for (int j = 0; j < k; ++j) {
-        if (!in_lds && j > 0 && !(w[j] - w[j - 1] <= ctol)) cstart = j;
-        const int i0 = in_lds ? 0 : cstart;
-        for (int pass = 0; pass < 2; ++pass) {
-            if (j > i0) {
-                // coef[i] = z_i . z_j, one wave per i, lanes over rows
-                for (int i = i0 + wave; i < j; i += nw) {
-                    double sacc = 0.0;
-                    for (int r = lane; r < n; r += 64) sacc += Z[(int64_t)r * ldz + i] * Z[(int64_t)r * ldz + j];
-                    for (int off = 32; off > 0; off >>= 1) sacc += __shfl_xor(sacc, off);
-                    if (lane == 0) coef[i] = sacc;
-                }
-                __syncthreads();
-                for (int r = t; r < n; r += nt) {
-                    double sv = Z[(int64_t)r * ldz + j];
-                    for (int i = i0; i < j; ++i) sv -= coef[i] * Z[(int64_t)r * ldz + i];
-                    Z[(int64_t)r * ldz + j] = sv;
-                }
-                __syncthreads();
+    for (int pass = 0; pass < 2; ++pass) {
+        if (j > i0) {
+            // coef[i - i0] = z_i . z_j, one wave per i, lanes over rows
+            for (int i = i0 + wave; i < j; i += nw) {
+                double sacc = 0.0;
+                for (int r = lane; r < n; r += 64) sacc += Z[r * ldz + i] * Z[r * ldz + j];
+                for (int off = 32; off > 0; off >>= 1) sacc += __shfl_xor(sacc, off);
+                if (lane == 0) coef[i - i0] = sacc;
             }
-            double pn = 0.0;
+            __syncthreads();
             for (int r = t; r < n; r += nt) {
-                const double vv = Z[(int64_t)r * ldz + j];
-                pn += vv * vv;
+                double sv = Z[r * ldz + j];
+                for (int i = i0; i < j; ++i) sv -= coef[i - i0] * Z[r * ldz + i];
+                Z[r * ldz + j] = sv;
             }
-            const double nn = block_sum(pn, red);
-            const double inv = nn > 0 ? 1.0 / sqrt(nn) : 0.0;
-            for (int r = t; r < n; r += nt) Z[(int64_t)r * ldz + j] *= inv;
             __syncthreads();
         }
+        double pn = 0.0;
+        for (int r = t; r < n; r += nt) {
+            const double vv = Z[r * ldz + j];
+            pn += vv * vv;
+        }
+        const double nn = block_sum(pn, red);
+        const double inv = nn > 0 ? 1.0 / sqrt(nn) : 0.0;
+        for (int r = t; r < n; r += nt) Z[r * ldz + j] *= inv;
+        __syncthreads();
     }
-    if (in_lds)
-        for (int i = t; i < n * k; i += nt) Zg[i] = Zl[(i / k) * ldz + i % k];
+}
+
+// Every column against all earlier ones, Z in LDS (k > 64 with n k small).
+__global__ void __launch_bounds__(1024) k_orth(double *__restrict__ Zg, int n, int k) {
+    extern __shared__ unsigned char smem_raw[];
+    double *coef = reinterpret_cast<double *>(smem_raw);   // [k]
+    double *red = coef + k;                                 // [16]
+    double *Z = red + 16;                                   // [n][k + 1] (padded rows: no bank conflicts)
+    for (int i = threadIdx.x; i < n * k; i += blockDim.x) Z[(i / k) * (k + 1) + i % k] = Zg[i];
+    __syncthreads();
+    for (int j = 0; j < k; ++j) gs_column(Z, k + 1, n, 0, j, coef, red);
+    for (int i = threadIdx.x; i < n * k; i += blockDim.x) Zg[i] = Z[(i / k) * (k + 1) + i % k];
+}
+
+// Larger Z: only within clusters of eigenvalues closer than ctol (vectors of
+// separated eigenvalues are already orthogonal to ~ n eps ||T|| / gap, the
+// backward error of the inverse-iteration solves over the gap, and unit).  One
+// workgroup per column, the one of a cluster's first column takes the whole
+// cluster and the others leave, so clusters run side by side and a column
+// on its own costs nothing (all of n = 512, no clusters: 2066 us as one workgroup over every
+// column, 9 us so).
+__global__ void __launch_bounds__(1024) k_orth_clusters(double *__restrict__ Z, int n, int k,
+                                                        const double *__restrict__ w, double ctol_rel,
+                                                        const double *__restrict__ dd,
+                                                        const double *__restrict__ ee) {
+    extern __shared__ double coef[];   // [k]
+    __shared__ double red[48];
+    const int j0 = blockIdx.x;
+    const double ctol = ctol_rel * fmax(tri_bounds(dd, ee, n, red).tnorm, 1e-300);
+    __syncthreads();   // red is used again
+    if (j0 > 0 && w[j0] - w[j0 - 1] <= ctol) return;
+    int j1 = j0 + 1;
+    while (j1 < k && w[j1] - w[j1 - 1] <= ctol) ++j1;
+    if (j1 == j0 + 1) return;
+    for (int j = j0; j < j1; ++j) gs_column(Z, k, n, j0, j, coef, red);
 }
 
 // CholQR, twice, of the columns of Z [n][k] (k <= 64, n <= 256, all in LDS):
@@ -1289,100 +1139,26 @@ __global__ void __launch_bounds__(256) k_orth_chol(double *__restrict__ Zg, int 
     if (t == 0 && fail) atomicOr(status, 2);
 }
 
-// V[:, c] = H_0 ... H_{n-2} Z[:, c] for a chunk of cw columns held in LDS.
-// Reflectors are staged into LDS nrefl at a time (the host picks cw and nrefl
-// so that both fit; the staging depth does not change the arithmetic).
-__global__ void __launch_bounds__(256) k_unmtr(const cd *__restrict__ A, int64_t lda, int n, int k,
-                                               int cw, int nrefl, const cd *__restrict__ tau,
-                                               const double *__restrict__ Z, cd *__restrict__ V,
-                                               int64_t ldv) {
-    extern __shared__ unsigned char smem_raw[];
-    cd *Vs = reinterpret_cast<cd *>(smem_raw);   // [n][cw + 1]
-    cd *vb = Vs + (size_t)n * (cw + 1);          // [nrefl][n] staged reflectors
-    cd *sp = vb + (size_t)nrefl * n;             // [blockDim] partial dots
-    cd *sc = sp + blockDim.x;                    // [cw]
-    const int t = threadIdx.x, nt = blockDim.x;
-    const int c0 = blockIdx.x * cw;
-    const int ncol = min(cw, k - c0);
-    const int LD = cw + 1;
-    for (int i = t; i < n * cw; i += nt) {
-        const int r = i / cw, c = i % cw;
-        Vs[r * LD + c] = cd{c < ncol ? Z[(int64_t)r * k + c0 + c] : 0.0, 0.0};
-    }
-    const int parts = nt / cw;   // threads per column in the dot products
-    for (int jhi = n - 2; jhi >= 0; jhi -= nrefl) {
-        const int jlo = max(0, jhi - nrefl + 1);
-        __syncthreads();
-        // stage reflectors jhi..jlo: slot q holds reflector jhi - q, rows j+1..n-1
-        for (int idx = t; idx < nrefl * n; idx += nt) {
-            const int q = idx / n, i = idx % n;
-            const int j = jhi - q;
-            if (j >= jlo) {
-                const int L = n - j - 1;
-                vb[q * n + i] = (i >= L) ? cd{0.0, 0.0} : (i == 0) ? cd{1.0, 0.0} : A[(int64_t)j * lda + j + 1 + i];
-            }
-        }
-        __syncthreads();
-        for (int j = jhi; j >= jlo; --j) {
-            const cd tj = tau[j];
-            if (tj.x == 0.0 && tj.y == 0.0) continue;
-            const cd *vv = vb + (jhi - j) * n;
-            const int L = n - j - 1;
-            {
-                const int c = t % cw, p = t / cw;
-                double sr0 = 0.0, si0 = 0.0, sr1 = 0.0, si1 = 0.0;
-                if (p < parts) {
-                    int i = p;
-                    for (; i + parts < L; i += 2 * parts) {
-                        const cd a0 = vv[i], x0 = Vs[(j + 1 + i) * LD + c];
-                        const cd a1 = vv[i + parts], x1 = Vs[(j + 1 + i + parts) * LD + c];
-                        sr0 += a0.x * x0.x + a0.y * x0.y;
-                        si0 += a0.x * x0.y - a0.y * x0.x;
-                        sr1 += a1.x * x1.x + a1.y * x1.y;
-                        si1 += a1.x * x1.y - a1.y * x1.x;
-                    }
-                    for (; i < L; i += parts) {
-                        const cd a0 = vv[i], x0 = Vs[(j + 1 + i) * LD + c];
-                        sr0 += a0.x * x0.x + a0.y * x0.y;
-                        si0 += a0.x * x0.y - a0.y * x0.x;
-                    }
-                }
-                sp[t] = cd{sr0 + sr1, si0 + si1};
-            }
-            __syncthreads();
-            if (t < cw) {
-                double sr = 0.0, si = 0.0;
-                for (int p = 0; p < parts; ++p) {
-                    sr += sp[p * cw + t].x;
-                    si += sp[p * cw + t].y;
-                }
-                sc[t] = cmulz(tj, cd{sr, si});
-            }
-            __syncthreads();
-            for (int i = t; i < L * cw; i += nt) {
-                const int r = i / cw, c = i % cw;
-                const cd pr = cmulz(vv[r], sc[c]);
-                cd &x = Vs[(j + 1 + r) * LD + c];
-                x.x -= pr.x;
-                x.y -= pr.y;
-            }
-            __syncthreads();
-        }
-    }
-    __syncthreads();
-    for (int i = t; i < n * ncol; i += nt) {
-        const int c = i / n, r = i % n;
-        V[(int64_t)(c0 + c) * ldv + r] = Vs[r * LD + c];
-    }
-}
-
 // CholQR applied twice to the real eigenvector block Z [n x k] (k <= 64,
-// n <= 217), in LDS, 1024 threads.  G = Z^T Z and Z R^-1 run on the FP64
+// n <= 208), in LDS, 1024 threads.  G = Z^T Z and Z R^-1 run on the FP64
 // matrix cores (16 x 16 output tiles, one to three per wave).  The factor
 // comes from elimination on [G | I] as in k_chol_inv (pivot row broadcast
 // through LDS, one barrier per step, rows kept unscaled until the end: the
 // augmented half becomes L^-1 and R^-T = D^-1/2 L^-1), with 2 x 2 tiles per
-// thread on a 32 x 32 grid.  Columns >= k carry an identity block of G.
+// thread on a 32 x 32 grid.  Columns >= k carry an identity block of G, whose
+// pivots change nothing: the elimination ends at k.
+// The elimination, k/2 barrier steps of latency, was most of the time, and it
+// is left out where G is within kOc2Near of the identity: there R^-1 = I - F
+// with F the strict upper part of G - I plus half its diagonal, off by F^2,
+// below (64 kOc2Near)^2 = 4e-17, and one pass is enough.  Inverse
+// iteration gives that for eigenvalues with relative gaps above ~1e-6, that is
+// nearly every Rayleigh-Ritz problem; a cluster takes the elimination, and its
+// second pass is near the identity again.  n = 192, k = 64: 92 -> 20 us;
+// n = 48, k = 16: 67 -> 6.3 us.
+constexpr double kOc2Near = 1e-10;
+// upper 16 x 16 tiles of G, then the lower ones (left zero)
+__constant__ const unsigned char kOc2Tile[16] = {0x00, 0x01, 0x02, 0x03, 0x11, 0x12, 0x13, 0x22,
+                                                 0x23, 0x33, 0x10, 0x20, 0x30, 0x21, 0x31, 0x32};
 constexpr int kOc2Ld = 68;   // LDS row stride of Z (doubles)
 constexpr int kOc2Lr = 65;   // LDS row stride of G and of R^-1
 __host__ __device__ constexpr size_t orth_chol2_lds(int n) {
@@ -1408,17 +1184,34 @@ __global__ void __launch_bounds__(1024) k_orth_chol2(double *__restrict__ Zg, in
     __syncthreads();
     bool fail = false;
     for (int pass = 0; pass < 2; ++pass) {
-        {   // G = Z^T Z: wave w computes the 16 x 16 tile (w / 4, w % 4)
-            const int ra = 16 * (wave >> 2), cb = 16 * (wave & 3);
-            v4d acc = {0.0, 0.0, 0.0, 0.0};
-            for (int k0 = 0; k0 < n16; k0 += 4) {
-                const double *zr = Z + (size_t)(k0 + lg) * kOc2Ld;
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(zr[ra + li], zr[cb + li], acc, 0, 0, 0);
+        const int tile = kOc2Tile[wave], ra = 16 * (tile >> 4), cg = 16 * (tile & 15);
+        v4d gacc = {0.0, 0.0, 0.0, 0.0};
+        if (ra <= cg && cg < k) {   // G = Z^T Z, upper tiles, one per wave
+            v4d odd = {0.0, 0.0, 0.0, 0.0};
+            for (int k0 = 0; k0 < n16; k0 += 8) {
+                const double *z0 = Z + (size_t)(k0 + lg) * kOc2Ld;
+                gacc = __builtin_amdgcn_mfma_f64_16x16x4f64(z0[ra + li], z0[cg + li], gacc, 0, 0, 0);
+                const double *z1 = z0 + 4 * kOc2Ld;
+                odd = __builtin_amdgcn_mfma_f64_16x16x4f64(z1[ra + li], z1[cg + li], odd, 0, 0, 0);
             }
+            gacc += odd;
+        }
+        bool away = false;   // some element of G not within kOc2Near of the identity (or not finite)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) Gs[(ra + lg + 4 * r) * kOc2Lr + cb + li] = acc[r];
+        for (int r = 0; r < 4; ++r) {
+            const int a = ra + lg + 4 * r, b = cg + li;
+            away |= a <= b && b < k && !(fabs(gacc[r] - (a == b ? 1.0 : 0.0)) <= kOc2Near);
+        }
+        const bool near = !__syncthreads_or(away);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int a = ra + lg + 4 * r, b = cg + li;
+            double v = gacc[r];
+            if (near) v = a < b ? -v : a == b ? 1.5 - 0.5 * v : 0.0;   // I - F
+            Gs[a * kOc2Lr + b] = v;
         }
         __syncthreads();
+        if (!near) {
         double g[2][2], u[2][2], dpiv[2] = {1.0, 1.0};
 #pragma unroll
         for (int ia = 0; ia < 2; ++ia)
@@ -1435,7 +1228,7 @@ __global__ void __launch_bounds__(1024) k_orth_chol2(double *__restrict__ Zg, in
         __syncthreads();
         // two pivots per barrier (as in k_chol_inv): rows j, j + 1 arrive with
         // the pivots < j applied; row j + 1 after pivot j is formed locally
-        for (int j = 0; j < 64; j += 2) {
+        for (int j = 0; j < k; j += 2) {
             const int bsel = (j >> 1) & 1;
             const double *r0g = pg + 128 * bsel, *r1g = r0g + 64, *r0u = pu + 128 * bsel, *r1u = r0u + 64;
             double d0 = r0g[j];
@@ -1482,7 +1275,7 @@ __global__ void __launch_bounds__(1024) k_orth_chol2(double *__restrict__ Zg, in
                         u[ia][ib] -= m0[ia] * u0[ib] + m1[ia] * u1[ib];
                     }
                 }
-                if (j + 2 < 64 && a0 == j + 2) {
+                if (j + 2 < k && a0 == j + 2) {
                     double *ng = pg + 128 * (bsel ^ 1), *nu = pu + 128 * (bsel ^ 1);
 #pragma unroll
                     for (int ia = 0; ia < 2; ++ia) {
@@ -1503,12 +1296,15 @@ __global__ void __launch_bounds__(1024) k_orth_chol2(double *__restrict__ Zg, in
             for (int ib = 0; ib < 2; ++ib) Gs[(b0 + ib) * kOc2Lr + a0 + ia] = u[ia][ib] * isd;
         }
         __syncthreads();
-        {   // Z <- Z R^-1: wave w computes column tile w % 4 of row tiles w / 4 + 4 i
-            const int cb = 16 * (wave & 3);
+        }
+        {   // Z <- Z R^-1: wave w computes one column tile of row tiles w / 4 + 4 i
+            // (rows of R^-1 down to the tile's last column; the column tiles are
+            // dealt so that every SIMD gets each of them once)
+            const int cb = 16 * ((wave + (wave >> 2)) & 3);
             v4d acc[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) acc[i] = v4d{0.0, 0.0, 0.0, 0.0};
-            for (int k0 = 0; k0 < 64; k0 += 4) {
+            for (int k0 = 0; k0 < cb + 16; k0 += 4) {
                 const double b = Gs[(k0 + lg) * kOc2Lr + cb + li];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -1531,6 +1327,7 @@ __global__ void __launch_bounds__(1024) k_orth_chol2(double *__restrict__ Zg, in
             }
         }
         __syncthreads();
+        if (near) break;
     }
     for (int i = t; i < n * k; i += nt) Zg[i] = Z[(i / k) * kOc2Ld + i % k];
     if (t == 0 && fail) atomicOr(status, 2);
@@ -1541,13 +1338,17 @@ __global__ void __launch_bounds__(1024) k_orth_chol2(double *__restrict__ Zg, in
 // Reflectors are applied in groups of kUwRing with a ring of kUwRing
 // reflectors loaded ahead, so the loads of one group overlap the work of the
 // previous one.
+// The ring is 8 deep up to n = 256 and shorter above, by registers.  One
+// reflector is a chain of ~1000 cycles up to n = 512, so a wave of its own per
+// column beats workgroups with 32 columns in LDS and four barriers a reflector
+// (n = k = 512: 1884 -> 481 us).
 constexpr int kUwCols = 1;
-constexpr int kUwRing = 8;
 template <int RPL>
 __global__ void __launch_bounds__(64) k_unmtr_w(const cd *__restrict__ A, int64_t lda, int n, int k,
                                                 const cd *__restrict__ tau,
                                                 const double *__restrict__ Z, cd *__restrict__ V,
                                                 int64_t ldv) {
+    constexpr int kUwRing = RPL <= 4 ? 8 : RPL <= 8 ? 4 : 2;
     const int l = threadIdx.x;
     const int c0 = blockIdx.x * kUwCols;
     cd x[RPL][kUwCols];
@@ -1613,11 +1414,6 @@ __global__ void __launch_bounds__(64) k_unmtr_w(const cd *__restrict__ A, int64_
             if (r < n) V[(int64_t)(c0 + c) * ldv + r] = x[q][c];
         }
     }
-}
-
-__global__ void k_check_w(const double *w, int k, int *status) {
-    for (int i = threadIdx.x; i < k; i += blockDim.x)
-        if (!isfinite(w[i])) atomicOr(status, 4);
 }
 
 }  // namespace
@@ -1686,36 +1482,28 @@ void launch_heev_f64(cd *A, int64_t lda, int n, int k, double *w, cd *V, int64_t
             hipLaunchKernelGGL(k_trd_step, dim3(1), dim3(1024), 0, st, A, lda, n, j, S, d, e, tau);
         }
     }
-    // 2. eigenvalues
-    const size_t sm2 = 2 * (size_t)n * 8;
-    // one workgroup per eigenvalue, spread over k CUs
+    // 2. eigenvalues, one workgroup each, spread over k CUs
     const bool lowp = fp32_reduction && n <= 32 * kRfMaxT;
-    const double tol = lowp ? (double)FLT_EPSILON : DBL_EPSILON;
-    switch ((n + 63) / 64) {
-        case 1: hipLaunchKernelGGL(k_stebz_w<1>, dim3(k), dim3(kStebzThreads), 0, st, d, e, n, k, w, tol); break;
-        case 2: hipLaunchKernelGGL(k_stebz_w<2>, dim3(k), dim3(kStebzThreads), 0, st, d, e, n, k, w, tol); break;
-        case 3: hipLaunchKernelGGL(k_stebz_w<3>, dim3(k), dim3(kStebzThreads), 0, st, d, e, n, k, w, tol); break;
-        case 4: hipLaunchKernelGGL(k_stebz_w<4>, dim3(k), dim3(kStebzThreads), 0, st, d, e, n, k, w, tol); break;
-        default: hipLaunchKernelGGL(k_stebz, dim3(k), dim3(kStebzThreads), sm2, st, d, e, n, k, w); break;
-    }
-    // 3. inverse iteration
-    if (n <= 256) {
-        switch ((n + 63) / 64) {
-            case 1: hipLaunchKernelGGL(k_stein_w<1>, dim3(k), dim3(64), 0, st, d, e, n, k, w, Z); break;
-            case 2: hipLaunchKernelGGL(k_stein_w<2>, dim3(k), dim3(64), 0, st, d, e, n, k, w, Z); break;
-            case 3: hipLaunchKernelGGL(k_stein_w<3>, dim3(k), dim3(64), 0, st, d, e, n, k, w, Z); break;
-            default: hipLaunchKernelGGL(k_stein_w<4>, dim3(k), dim3(64), 0, st, d, e, n, k, w, Z); break;
+    hipLaunchKernelGGL(k_stebz, dim3(k), dim3(kStebzThreads), (size_t)n * 16, st, d, e, n, w,
+                       lowp ? (double)FLT_EPSILON : DBL_EPSILON, status);
+    // 3. inverse iteration, one wave per eigenvalue
+    const int rpl = (n + 63) / 64;
+    auto by_rpl = [&](auto &&f) {
+        switch (rpl) {
+            case 1: f(std::integral_constant<int, 1>{}); break;
+            case 2: f(std::integral_constant<int, 2>{}); break;
+            case 3: f(std::integral_constant<int, 3>{}); break;
+            case 4: f(std::integral_constant<int, 4>{}); break;
+            case 5: case 6: f(std::integral_constant<int, 6>{}); break;
+            case 7: case 8: f(std::integral_constant<int, 8>{}); break;
+            case 9: case 10: case 11: case 12: f(std::integral_constant<int, 12>{}); break;
+            default: f(std::integral_constant<int, 16>{}); break;
         }
-    } else {
-    const size_t budget = 150 * 1024;
-    int E = (int)((budget - 16 * (size_t)n) / (48 * (size_t)n));
-    E = std::max(1, std::min(4, E));   // few eigenvalues per workgroup: spread over CUs
-    const size_t sm3 = 16 * (size_t)n + 48 * (size_t)n * E;
-    ensure_smem_limit((const void *)k_stein, sm3);
-    hipLaunchKernelGGL(k_stein, dim3((k + E - 1) / E), dim3(64), sm3, st, d, e, n, k, E, w, Z);
-    }
+    };
+    by_rpl([&](auto q) { hipLaunchKernelGGL(k_stein_w<decltype(q)::value>, dim3(k), dim3(64), 0, st, d, e, n, k, w, Z); });
     // 4. orthogonalisation
     const size_t smc = ((size_t)n * (k + 1) + (size_t)k * (k + 1) + k) * 8;
+    const size_t sml = ((size_t)n * (k + 1) + k + 16) * 8;
     if (k <= 64 && orth_chol2_lds(n) <= 150 * 1024) {
         const size_t sm = orth_chol2_lds(n);
         ensure_smem_limit((const void *)k_orth_chol2, sm);
@@ -1723,43 +1511,17 @@ void launch_heev_f64(cd *A, int64_t lda, int n, int k, double *w, cd *V, int64_t
     } else if (k <= kOrthMaxK && n <= 256 && smc <= 150 * 1024) {
         ensure_smem_limit((const void *)k_orth_chol, smc);
         hipLaunchKernelGGL(k_orth_chol, dim3(1), dim3(256), smc, st, Z, n, k, status);
+    } else if (sml <= 132 * 1024) {
+        ensure_smem_limit((const void *)k_orth, sml);
+        hipLaunchKernelGGL(k_orth, dim3(1), dim3(1024), sml, st, Z, n, k);
     } else {
-    const bool in_lds = (size_t)n * (k + 1) * 8 + (size_t)(k + 1024) * 8 <= 140 * 1024;
-    const size_t sm4 = (size_t)(k + 1024) * 8 + (in_lds ? (size_t)n * (k + 1) * 8 : 0);
-    ensure_smem_limit((const void *)k_orth, sm4);
-    hipLaunchKernelGGL(k_orth, dim3(1), dim3(1024), sm4, st, Z, n, k, in_lds ? 1 : 0, w, 2e-5, d, e);
+        hipLaunchKernelGGL(k_orth_clusters, dim3(k), dim3(1024), (size_t)k * 8, st, Z, n, k, w, 2e-5, d, e);
     }
     // 5. back-transform
-    if (n <= 256) {
-        const dim3 g((k + kUwCols - 1) / kUwCols);
-        switch ((n + 63) / 64) {
-            case 1: hipLaunchKernelGGL(k_unmtr_w<1>, g, dim3(64), 0, st, A, lda, n, k, tau, Z, V, ldv); break;
-            case 2: hipLaunchKernelGGL(k_unmtr_w<2>, g, dim3(64), 0, st, A, lda, n, k, tau, Z, V, ldv); break;
-            case 3: hipLaunchKernelGGL(k_unmtr_w<3>, g, dim3(64), 0, st, A, lda, n, k, tau, Z, V, ldv); break;
-            default: hipLaunchKernelGGL(k_unmtr_w<4>, g, dim3(64), 0, st, A, lda, n, k, tau, Z, V, ldv); break;
-        }
-        hipLaunchKernelGGL(k_check_w, dim3(1), dim3(256), 0, st, w, k, status);
-        PW_HIP(hipGetLastError());
-        return;
-    }
-    // columns per workgroup and staged reflectors: up to 32 and 8; past n ~ 930
-    // both shrink (columns down to 4 first, then the staging depth) to fit LDS
-    int cw = 32, nrefl = 8;
-    auto sm5_of = [&](int w_, int r_) {
-        return (size_t)n * (w_ + 1) * 16 + (size_t)r_ * n * 16 + 256 * 16 + (size_t)w_ * 16;
-    };
-    while (sm5_of(cw, nrefl) > 150 * 1024) {
-        if (cw > 4) cw /= 2;
-        else if (nrefl > 1) nrefl /= 2;
-        else if (cw > 1) cw /= 2;
-        else break;
-    }
-    const size_t sm5 = sm5_of(cw, nrefl);
-    PW_REQUIRE(sm5 <= 150 * 1024, PW_ERR_ARG, "eigenproblem too large for the back-transform");
-    ensure_smem_limit((const void *)k_unmtr, sm5);
-    hipLaunchKernelGGL(k_unmtr, dim3((k + cw - 1) / cw), dim3(256), sm5, st, A, lda, n, k, cw, nrefl, tau,
-                       Z, V, ldv);
-    hipLaunchKernelGGL(k_check_w, dim3(1), dim3(256), 0, st, w, k, status);
+    by_rpl([&](auto q) {
+        hipLaunchKernelGGL(k_unmtr_w<decltype(q)::value>, dim3((k + kUwCols - 1) / kUwCols), dim3(64), 0, st, A, lda, n,
+                           k, tau, Z, V, ldv);
+    });
     PW_HIP(hipGetLastError());
 }
 
