@@ -201,7 +201,8 @@ pw_status pw_apply_H_batch(pw_ctx const *ctxs, int32_t nk, const void *const *X,
  * split-K target that of the Gram sums, so both may change the rounding. */
 typedef struct {
     int32_t fft_sticks_per_block;   /* z passes: sticks per workgroup, 0 or 1..64 (default 16) */
-    int32_t fft_plane_rows;         /* plane pass: row chunk, 0 or 1..128 (default 48, capped by LDS) */
+    int32_t fft_plane_rows;         /* plane pass: rows a workgroup works on at once (a cap on its waves),
+                                       0 or 1..128 (default: what LDS and registers hold) */
     int32_t gemm_split_workgroups;  /* split-K TN target workgroups, 0 or 1..1024 (default 1024) */
     double apply_ms_default, apply_ms_tuned;   /* local H X of nb bands */
     double gemm_ms_default, gemm_ms_tuned;     /* 3m x 3m Gram over npw (+ projector overlaps) */

@@ -19,7 +19,8 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(ROOT, "_build", "obj")
 LIB = os.path.join(HERE, "libpwlobpcg.so")
 ARCH = "gfx950"
-SOURCES = ["fft_apply.hip", "gemm.hip", "dense.hip", "vec.hip", "noalloc.hip", "runtime.cpp"]
+SOURCES = ["fft_f64_large.hip", "fft_f64_small.hip", "fft_f32_large.hip", "fft_f32_small.hip", "fft_apply.hip",
+           "gemm.hip", "dense.hip", "vec.hip", "noalloc.hip", "runtime.cpp"]
 FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC",
          "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
          # packed FP32 instructions are kept out of every kernel

@@ -212,6 +212,35 @@ struct Dft<5, S, T> {
     }
 };
 
+// DFT of 8 points whose inputs 2..5 are zero (v[2..5] is not read)
+template <int S, class T>
+__device__ __forceinline__ void dft8_quarters_in(cpx<T> *v) {
+    const cpx<T> b0 = mul_si<S>(v[6]), b1 = mul_si<S>(v[7]);
+    // radix-4 halves over inputs 0, 6 and 1, 7
+    const cpx<T> t0 = cadd(v[0], v[6]), t1 = csub(v[0], b0), t2 = csub(v[0], v[6]), t3 = cadd(v[0], b0);
+    const cpx<T> u0 = cadd(v[1], v[7]), u1 = twc<S, 1, 8>(csub(v[1], b1)), u2 = mul_si<S>(csub(v[1], v[7])),
+                 u3 = twc<S, 3, 8>(cadd(v[1], b1));
+    v[0] = cadd(t0, u0);
+    v[4] = csub(t0, u0);
+    v[1] = cadd(t1, u1);
+    v[5] = csub(t1, u1);
+    v[2] = cadd(t2, u2);
+    v[6] = csub(t2, u2);
+    v[3] = cadd(t3, u3);
+    v[7] = csub(t3, u3);
+}
+// DFT of 8 points of which only outputs 0, 1, 6 and 7 are formed
+template <int S, class T>
+__device__ __forceinline__ void dft8_quarters_out(cpx<T> *v) {
+    cpx<T> e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+    Dft<4, S, T>::run(e);
+    Dft<4, S, T>::run(o);
+    v[0] = cadd(e[0], o[0]);
+    v[1] = cadd(e[1], twc<S, 1, 8>(o[1]));
+    v[6] = csub(e[2], mul_si<S>(o[2]));
+    v[7] = csub(e[3], twc<S, 3, 8>(o[3]));
+}
+
 // ---- factorisation of N into R1 * R2 ----------------------------------------
 constexpr bool smooth(int r) {
     while (r % 2 == 0) r /= 2;

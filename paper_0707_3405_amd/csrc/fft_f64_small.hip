@@ -1,0 +1,19 @@
+// H.X passes, double, the small FFT sizes.
+#include "fft_apply.h"
+
+namespace pw {
+
+bool run_apply_small(const ApplyItems<double> &items, int nk, const double *v, int nb, hipStream_t st) {
+    switch (items.it[0].sp.n) {
+#define PW_CASE(NN)                                 \
+    case NN:                                        \
+        run_apply<NN, double>(items, nk, v, nb, st); \
+        return true;
+        PW_FFT_SIZES_SMALL(PW_CASE)
+#undef PW_CASE
+        default:
+            return false;
+    }
+}
+
+}  // namespace pw

@@ -49,11 +49,13 @@ struct SphereDev {
     int32_t ldst = 0;         // padded stick count (leading dim of stick buffers)
     int32_t ncx = 0;          // kept x columns (n_x in [xmin, xmin + ncx))
     int32_t xmin = 0;
+    int32_t quarter = 0;      // 1: every n_x, n_y of the sphere lies in [-n/4, n/4)
     int32_t *st_start = nullptr;  // [nst]
     int32_t *st_len = nullptr;    // [nst]
     int32_t *st_z0 = nullptr;     // [nst] signed n_z of the first element
     int32_t *st_y = nullptr;      // [nst] grid y index (n_y mod n)
     int32_t *st_xc = nullptr;     // [nst] kept-column index n_x - xmin
+    int32_t *xc_start = nullptr;  // [ncx + 1] first stick of each kept column
     int32_t *g_map = nullptr;     // [npw] (stick * n + (n_z mod n))
     double *kin = nullptr;        // [npw] 1/2 |k+G|^2
     double *twid = nullptr;       // [n] exp(+2 pi i j / n), interleaved
@@ -75,12 +77,13 @@ void launch_fft_apply(const SphereDev &sp, const double *v_zyx, const cd *X, int
 // complex64 form: v_zyx as float
 void launch_fft_apply(const SphereDev &sp, const float *v_zyx, const cf *X, int64_t ldx,
                       cf *Y, int64_t ldy, int nb, cf *S, hipStream_t st);
-// Density: rho_zyx[z][y][x] += sum_b occ[b] |psi_b|^2 for nb columns of X (psi
-// = inverse transform of the sphere coefficients, no 1/sqrt(Omega)); then
-// rho[x][y][z] = scale * rho_zyx[z][y][x].
-void launch_density_accumulate(const SphereDev &sp, const cd *X, int64_t ldx, int nb,
-                               const double *occ, double *rho_zyx, cd *S, hipStream_t st);
-void launch_density_finish(const double *rho_zyx, int n, double scale, double *rho, hipStream_t st);
+// Density: part[g][z][y][x position] += sum of occ[b] |psi_b|^2 over the columns
+// b = g, g + groups, ... of X (psi = inverse transform of the sphere
+// coefficients, no 1/sqrt(Omega)); then rho[x][y][z] = scale * the groups' sum.
+void launch_density_accumulate(const SphereDev &sp, const cd *X, int64_t ldx, int nb, const double *occ, double *part,
+                               int groups, cd *S, hipStream_t st);
+void launch_density_finish(const double *part, int n, int groups, double scale, double *rho, hipStream_t st);
+int density_resident(const SphereDev &sp);   // plane workgroups of the density resident per CU
 bool fft_size_supported(int n);
 std::vector<int> fft_supported_sizes();
 // One k-point of a multi-k-point apply: its sphere, X and Y, its stick buffer.
@@ -107,7 +110,7 @@ void launch_fft_apply_batch(const FftApplyItem<float> *items, int nk, const floa
 // record of the context whose API call is running on this host thread.
 struct Tuning {
     int fft_spb = 0;        // sticks per workgroup of the z passes
-    int fft_rb = 0;         // row chunk of the plane pass (capped by LDS)
+    int fft_rb = 0;         // rows a plane workgroup works on at once (a cap on its waves)
     int tn_split_wgs = 0;   // target workgroup count of a split-K TN launch
     int fft_r2 = 0;         // second factor R2 of the radix split N = R1 R2 (0: default)
 };

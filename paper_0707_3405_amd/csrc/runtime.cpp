@@ -292,6 +292,25 @@ size_t density_bytes(const pw_ctx_s &c, int chunk, int nb) {
     return align_up(a.used, 256);
 }
 
+// Band groups of the density's plane pass (n workgroups each, `resident` of them
+// per CU): the bands of a chunk are dealt over the groups, and each group costs
+// a read and a write of its own sum of the grid.  One group left 160 of the 256
+// CUs idle at n = 96.  Rounds of workgroups times bands per group, at about
+// n^2 ns a plane, against 16 n^3 bytes a group at ~5 TB/s.
+int density_groups(int n, int resident, int nc, int most) {
+    const int slots = 256 * std::max(1, resident);
+    int best = 1;
+    double cost = HUGE_VAL;
+    for (int g = 1; g <= std::min(nc, most); ++g) {
+        const double c = (double)((n * g + slots - 1) / slots) * std::max(1, resident) * ((nc + g - 1) / g) + 3.2e-3 * n * g;
+        if (c < cost) {
+            cost = c;
+            best = g;
+        }
+    }
+    return best;
+}
+
 // the solver's plan, and enough for pw_density of up to M bands with the same block
 size_t plan_bytes(const pw_ctx_s &c, int M, int m, pw_precision prec) {
     size_t b = make_plan<cd>(c, M, m, nullptr).bytes;
@@ -929,7 +948,10 @@ void init_basis(pw_ctx_s *c, const double cell[9], const double kfrac[3], double
     PW_REQUIRE(npw > 0, PW_ERR_ARG, "empty plane-wave sphere");
     int mx[3] = {0, 0, 0};
     int xmin = 1 << 30, xmax = -(1 << 30);
+    bool quarter = N % 4 == 0;
     for (int64_t g = 0; g < npw; ++g) {
+        for (int j = 0; j < 2; ++j)
+            quarter = quarter && c->miller[3 * g + j] >= -N / 4 && c->miller[3 * g + j] < N / 4;
         for (int j = 0; j < 3; ++j) mx[j] = std::max(mx[j], std::abs(c->miller[3 * g + j]));
         xmin = std::min(xmin, c->miller[3 * g]);
         xmax = std::max(xmax, c->miller[3 * g]);
@@ -965,6 +987,7 @@ void init_basis(pw_ctx_s *c, const double cell[9], const double kfrac[3], double
     sp.ldst = (int32_t)align_up((size_t)nst, 16);
     sp.ncx = xmax - xmin + 1;
     sp.xmin = xmin;
+    sp.quarter = quarter;
     if (c->device < 0) {   // host-only context: tables stay on the host
         c->has_basis = true;
         *npw_out = npw;
@@ -982,6 +1005,10 @@ void init_basis(pw_ctx_s *c, const double cell[9], const double kfrac[3], double
     sp.st_z0 = up_i(st_z0);
     sp.st_y = up_i(st_y);
     sp.st_xc = up_i(st_xc);
+    std::vector<int32_t> xc_start(sp.ncx + 1, nst);   // sticks are ordered by n_x
+    for (int s = nst - 1; s >= 0; --s) xc_start[st_xc[s]] = s;
+    for (int x = sp.ncx - 1; x >= 0; --x) xc_start[x] = std::min(xc_start[x], xc_start[x + 1]);
+    sp.xc_start = up_i(xc_start);
     sp.g_map = up_i(g_map);
     sp.kin = c->dev_alloc<double>(npw);
     PW_HIP(hipMemcpy(sp.kin, c->kin.data(), npw * sizeof(double), hipMemcpyHostToDevice));
@@ -1576,20 +1603,22 @@ pw_status pw_density(pw_ctx c, const void *X, int64_t ldx, int32_t nb, const dou
         Arena a;
         a.base = c->ws;
         cd *S = a.take<cd>((size_t)chunk * c->n * c->sp.ldst);
-        double *rz = a.take<double>((size_t)n3);
         double *docc = a.take<double>((size_t)nb);
+        const int64_t room = (int64_t)(c->ws_bytes - align_up(a.used, 256)) / (n3 * 8);   // >= 1 by the check above
+        const int groups = density_groups(c->n, pw::density_resident(c->sp), std::min(chunk, nb), (int)std::min<int64_t>(room, 64));
+        double *part = a.take<double>((size_t)n3 * groups);
         hipStream_t st = c->stream;
-        pw::launch_zero(reinterpret_cast<cd *>(rz), n3 / 2, n3 / 2, 1, st);   // N is even
+        pw::launch_zero(reinterpret_cast<cd *>(part), n3 / 2 * groups, n3 / 2 * groups, 1, st);   // N is even
         PW_HIP(hipMemcpyAsync(docc, occ, sizeof(double) * nb, hipMemcpyHostToDevice, st));
         const cd *Xc = static_cast<const cd *>(X);
         for (int b0 = 0; b0 < nb; b0 += chunk) {
             const int nc = std::min(chunk, nb - b0);
-            pw::launch_density_accumulate(c->sp, Xc + (int64_t)b0 * ldx, ldx, nc, docc + b0, rz, S, st);
+            pw::launch_density_accumulate(c->sp, Xc + (int64_t)b0 * ldx, ldx, nc, docc + b0, part, groups, S, st);
         }
         const double *m = c->cell;
         const double omega = std::fabs(m[0] * (m[4] * m[8] - m[5] * m[7]) - m[1] * (m[3] * m[8] - m[5] * m[6]) +
                                        m[2] * (m[3] * m[7] - m[4] * m[6]));
-        pw::launch_density_finish(rz, c->n, 1.0 / omega, static_cast<double *>(rho), st);
+        pw::launch_density_finish(part, c->n, groups, 1.0 / omega, static_cast<double *>(rho), st);
         PW_HIP(hipStreamSynchronize(st));   // occ is read from host memory above
         return PW_OK;
     });
