@@ -203,7 +203,8 @@ typedef struct {
     int32_t fft_sticks_per_block;   /* z passes: sticks per workgroup, 0 or 1..64 (default 16) */
     int32_t fft_plane_rows;         /* plane pass: rows a workgroup works on at once (a cap on its waves),
                                        0 or 1..128 (default: what LDS and registers hold) */
-    int32_t gemm_split_workgroups;  /* split-K TN target workgroups, 0 or 1..1024 (default 1024) */
+    int32_t gemm_split_workgroups;  /* cap on the workgroups of a split-K TN product, 0 or 1..1024 (default
+                                       512 or, for long complex64 products, 768) */
     double apply_ms_default, apply_ms_tuned;   /* local H X of nb bands */
     double gemm_ms_default, gemm_ms_tuned;     /* 3m x 3m Gram over npw (+ projector overlaps) */
     int32_t fft_radix2;   /* radix split of the length-N FFTs: N = (N / R2) R2, both factors

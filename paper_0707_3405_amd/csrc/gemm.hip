@@ -167,7 +167,7 @@ __device__ __forceinline__ void mma_bf16(const cpx<float> (&a)[2][4], const cpx<
 template <class T, bool BF>
 __global__ void __launch_bounds__(kThreads)
     k_gemm_tn_lds(const cpx<T> *__restrict__ A, int64_t lda, const cpx<T> *__restrict__ B,
-                  int64_t ldb, int64_t K, int p, int q, int64_t kchunk, int tiles_m, int tiles_n,
+                  int64_t ldb, int64_t K, int p, int q, int tiles_m, int tiles_n,
                   int nsplit, cpx<T> *__restrict__ part, int herm) {
     using M = Mfma<T>;
     using v4 = typename M::v4;
@@ -193,8 +193,10 @@ __global__ void __launch_bounds__(kThreads)
     }
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int li = lane & 15, g = lane >> 4;
-    const int64_t kbeg = (int64_t)split * kchunk;
-    const int64_t kend = min(K, kbeg + kchunk);
+    // k-blocks [nkb split / nsplit, nkb (split + 1) / nsplit): chunks differ by at most one
+    const int64_t nkb = (K + KB - 1) / KB;
+    const int64_t kbeg = nkb * split / nsplit * KB;
+    const int64_t kend = min(K, nkb * (split + 1) / nsplit * KB);
 
     // global -> LDS assignment: instruction u covers columns 16 wave + 4u + g, rows li
     const cpx<T> *Ag[4];
@@ -285,13 +287,26 @@ __global__ void __launch_bounds__(kThreads)
     if (kbeg < kend) {
         gload(kbeg);
         lstore(0, kbeg);
+        // complex64: loads run two blocks ahead of their use and the stores come
+        // before the MFMAs, which go first among the waves of a SIMD: 512 x 512
+        // at K = 34208 493 -> 466 us.  FP64, whose MFMAs take twice as long, was
+        // 3-4 % slower so.
+        if constexpr (!kZeroAtLoad<T>) gload(kbeg + KB);
         __syncthreads();
         int buf = 0;
         for (int64_t kb = kbeg; kb < kend; kb += KB) {
-            const bool more = kb + KB < kend;
-            gload(kb + KB);   // past the chunk end: clamped, never stored
-            mma(buf);
-            if (more) lstore(buf ^ 1, kb + KB);
+            if constexpr (kZeroAtLoad<T>) {
+                const bool more = kb + KB < kend;
+                gload(kb + KB);   // past the chunk end: clamped, never stored
+                mma(buf);
+                if (more) lstore(buf ^ 1, kb + KB);
+            } else {
+                lstore(buf ^ 1, kb + KB);
+                gload(kb + 2 * KB);   // past the chunk end: clamped, stored as zeros and not used
+                __builtin_amdgcn_s_setprio(1);
+                mma(buf);
+                __builtin_amdgcn_s_setprio(0);
+            }
             __syncthreads();
             buf ^= 1;
         }
@@ -505,10 +520,13 @@ __global__ void __launch_bounds__(kThreads)
 // NN with the rows dealt out in 16-row blocks: workgroup (g, tn) takes row
 // blocks [g nblk / G, (g + 1) nblk / G) (at most kNnMaxRb of them) and the 64
 // columns of tile tn; its four waves each own 16 columns and every row block.
-// G is chosen so that the grid fills whole rounds of resident workgroups
-// instead of spilling a few 64-row tiles into an extra round (K = 34181 gives
-// 535 tiles of 64 rows for 512 resident workgroups).  Same LDS staging and
-// double buffering as k_gemm_nn_lds.
+// G is the fewest whole rounds of resident workgroups that keep to kNnMaxRb, so
+// that workgroups differ by one row block and no round is nearly empty.  (With
+// rounds of 4-block workgroups: FP64 748 x 64 at K = 82592, 2.5 rounds, 512 us,
+// 494 so; complex64, whose 768 slots 4-block workgroups left unevenly filled,
+// 432 x 64 at K = 34208 95 us, 80 so.)  A loop over such ranges in one round
+// costs the FP64 kernel its accumulation registers (115 -> 123 us).
+// Same LDS staging and double buffering as k_gemm_nn_lds.
 constexpr int kNnMaxRb = 5;
 template <class T>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 1 : 3)))
@@ -650,9 +668,6 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(s
     }
 }
 
-#ifndef PW_SPLIT_WGS
-#define PW_SPLIT_WGS 1024   // target workgroup count of a split-K launch
-#endif
 // compute units of the current device (queried once per process and device)
 int device_cu_count() {
     static std::atomic<int> cached[64];
@@ -668,31 +683,31 @@ int device_cu_count() {
     return n;
 }
 
-// for_size: an upper bound over every device (sizing the partial buffer on any
-// context, host-only ones included), without the CU-count cap
-int choose_split(int64_t K, int tiles, int target, bool for_size = false) {
-    // outputs of one or two 64 x 64 tiles (the CholQR Grams and the overlaps with
-    // [X P]) have too little work per k-block for several workgroups per CU: one
-    // round of at most one workgroup per CU, chunks of at least 4 k-blocks
-    const bool small = tiles <= 2;
-    const int64_t cap = (small && !for_size) ? std::min<int64_t>(target, device_cu_count()) : target;
-    int64_t ns = (small && !for_size) ? cap / tiles : (cap + tiles - 1) / tiles;
-    // chunks of at least 16 k-blocks (4 for small outputs), except for short K
-    // (coefficient-space products, K = 3m), which split down to single k-blocks
-    // (at most 16)
-    const int64_t minkb = small ? 4 : 16;
-    const int64_t kmax = std::max<int64_t>((K + 16 * minkb - 1) / (16 * minkb),
-                                           std::min<int64_t>((K + 15) / 16, 16));
-    if (ns > kmax) ns = kmax;
-    if (ns < 1) ns = 1;
-    return (int)ns;
+// Splits of K.  Every workgroup of the launch is resident at once (two per CU;
+// complex64 products of 20 k-blocks a workgroup or more take three) and all have
+// the same number of k-blocks to within one (one tile, or two in complex64: one per CU, as the sum of
+// more partials costs more than it saves): a few workgroups past the last
+// whole round had cost most of a round (432 x 64 at K = 34208: 518 workgroups
+// 178 us, 511 117; 1001, in two rounds with twice the partials, 144).  Short
+// products stop at chunks of 5 k-blocks (8 for one tile, whose partials are
+// summed by few workgroups), then of 3 while that leaves CUs idle, then at 64
+// workgroups (256 x 23 at K = 11392: 44 splits 39.7 us, 128 30.6; 96 x 96 at
+// K = 3425: 14 splits 33 us, 64 21).
+// target > 0: a cap on the workgroups from the tuning.
+int choose_split(int64_t K, int tiles, int target, bool cplx64) {
+    const int64_t nkb = (K + 15) / 16;
+    const int64_t slots = target > 0 ? target : tiles <= (cplx64 ? 2 : 1) ? 256 : (cplx64 && nkb * tiles >= 20 * 768) ? 768 : 512;
+    const int64_t longc = nkb / (tiles == 1 ? 8 : 5);
+    const int64_t mid = std::min<int64_t>(256 / tiles, nkb / 3);
+    const int64_t shortc = std::min<int64_t>(64 / tiles, nkb);
+    return (int)std::max<int64_t>(1, std::min(slots / tiles, std::max({longc, mid, shortc})));
 }
 
 }  // namespace
 
 size_t gemm_tn_part_elems(int64_t K, int p, int q, int *nsplit_out) {
     const int tiles = ((p + kTile - 1) / kTile) * ((q + kTile - 1) / kTile);
-    const int ns = choose_split(K, tiles, std::max(PW_SPLIT_WGS, kTnSplitMax), true);   // any tuned target fits
+    const int ns = choose_split(K, tiles, kTnSplitMax, false);   // the most any target gives
     if (nsplit_out) *nsplit_out = ns;
     return (size_t)ns * p * q;
 }
@@ -709,19 +724,14 @@ void gemm_tn_impl(const cpx<T> *A, int64_t lda, const cpx<T> *B, int64_t ldb, in
     herm = herm && p == q && tiles_m >= 2 && !scale_row && beta == 0.0;
     const int ntile = herm ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
     const size_t per_split = herm ? (size_t)ntile * kTile * kTile : (size_t)p * q;
-    const int target = thread_tuning().tn_split_wgs > 0 ? thread_tuning().tn_split_wgs : PW_SPLIT_WGS;
-    int ns = choose_split(K, ntile, target);
+    int ns = choose_split(K, ntile, thread_tuning().tn_split_wgs, sizeof(T) == 4);
     if ((size_t)ns * per_split > part_elems) ns = (int)(part_elems / per_split);
     PW_REQUIRE(ns >= 1, PW_ERR_NOMEM, "GEMM partial buffer too small");
-    int64_t kchunk = (K + ns - 1) / ns;
-    kchunk = (kchunk + 15) / 16 * 16;
-    ns = (int)((K + kchunk - 1) / kchunk);
-    if (ns < 1) ns = 1;
     const int total = ntile * ns;
     // partials in the block type (the buffer is sized for complex128)
     cpx<T> *pt = reinterpret_cast<cpx<T> *>(part);
     hipLaunchKernelGGL((k_gemm_tn_lds<T, BF>), dim3(total), dim3(kThreads), 0, st, A, lda, B, ldb, K, p, q,
-                       kchunk, tiles_m, tiles_n, ns, pt, herm ? 1 : 0);
+                       tiles_m, tiles_n, ns, pt, herm ? 1 : 0);
     const int64_t n = (int64_t)per_split;
     const unsigned rgroups = (unsigned)((n + 63) / 64);
     if (rgroups < 256)
@@ -741,10 +751,7 @@ void gemm_nn_impl(const cpx<T> *A, int64_t lda, const cd *C, int64_t ldc, int64_
     PW_REQUIRE(!((const void *)A == (const void *)Y) || q <= kTile, PW_ERR_ARG,
                "in-place block update needs q <= 64");
     if constexpr (!BF) {
-        // row groups of 4-5 blocks of 16 rows, sized to whole rounds of the
-        // resident workgroups when that keeps <= 5 blocks per group
         const int64_t nblk = (K + 15) / 16;
-        int64_t G = (nblk + 3) / 4;
         static std::atomic<int> per_cu{0};   // resident workgroups per CU of this kernel
         int occ = per_cu.load(std::memory_order_relaxed);
         if (!occ) {
@@ -753,13 +760,9 @@ void gemm_nn_impl(const cpx<T> *A, int64_t lda, const cd *C, int64_t ldc, int64_
             per_cu.store(occ, std::memory_order_relaxed);
         }
         const int64_t slots = (int64_t)occ * device_cu_count();
-        const int64_t rounds = (G * tiles_n + slots - 1) / slots;
-        if (nblk * tiles_n <= slots) {
-            G = nblk;   // short K (coefficient space): one block per workgroup, all resident
-        } else if (rounds > 1) {
-            const int64_t Gfit = (rounds - 1) * slots / tiles_n;
-            if (Gfit >= (nblk + kNnMaxRb - 1) / kNnMaxRb) G = Gfit;
-        }
+        const int64_t per_round = std::max<int64_t>(1, slots / tiles_n);
+        const int64_t rounds = (nblk + kNnMaxRb * per_round - 1) / (kNnMaxRb * per_round);
+        const int64_t G = std::min(nblk, rounds * per_round);
         hipLaunchKernelGGL(k_gemm_nn_rows<T>, dim3((unsigned)(G * tiles_n)), dim3(kThreads), 0, st, A, lda,
                            C, ldc, K, p, q, alpha, beta, Y, ldy, (int)G);
         PW_HIP(hipGetLastError());
