@@ -46,6 +46,68 @@ __device__ __forceinline__ float lane_read(float v, int lane) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
+template <int CTRL>
+__device__ __forceinline__ double dpp_mov(double x) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float x) {   // one 32-bit move
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+// sum over the 16 lanes of a DPP row; every lane of the row gets the same value
+template <class R>
+__device__ __forceinline__ R row16_sum(R x) {
+    x += dpp_mov<0xB1>(x);    // quad_perm [1,0,3,2]
+    x += dpp_mov<0x4E>(x);    // quad_perm [2,3,0,1]
+    x += dpp_mov<0x141>(x);   // row_half_mirror
+    x += dpp_mov<0x140>(x);   // row_mirror
+    return x;
+}
+template <class R>
+__device__ __forceinline__ R quad_sum(R x) {
+    x += dpp_mov<0xB1>(x);
+    x += dpp_mov<0x4E>(x);
+    return x;
+}
+// lanes whose DPP row is disabled by ROW_MASK read 0
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_rows(double x) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROW_MASK, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROW_MASK, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_rows(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROW_MASK, 0xF, false));
+}
+// Wave sum returned as a wave-uniform value, without LDS: the row sums, then
+// row_bcast:15 adds row 0 into row 1 and row 2 into row 3, row_bcast:31 adds
+// rows 0 + 1 into rows 2 and 3, and lane 63 holds the total (same order of
+// additions in every wave).
+template <class R>
+__device__ __forceinline__ R wave_total(R x) {
+    x = row16_sum(x);
+    x += dpp_rows<0x142, 0xA>(x);   // row_bcast:15
+    x += dpp_rows<0x143, 0xC>(x);   // row_bcast:31
+    return lane_read(x, 63);
+}
+
+// sum over the lanes with the same lane % TR (TR = 4, 8, 16, 32); every lane gets it
+template <int TR>
+__device__ __forceinline__ double stride_sum(double x) {
+    if constexpr (TR <= 4) x += dpp_mov<0x124>(x);   // row_ror:4
+    if constexpr (TR <= 8) x += dpp_mov<0x128>(x);   // row_ror:8
+    auto swap_sum = [&](auto swap) {
+        const auto lo = swap((unsigned)__double2loint(x)), hi = swap((unsigned)__double2hiint(x));
+        x = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    };
+    if constexpr (TR <= 16) swap_sum([](unsigned v) { return __builtin_amdgcn_permlane16_swap(v, v, false, false); });
+    swap_sum([](unsigned v) { return __builtin_amdgcn_permlane32_swap(v, v, false, false); });
+    return x;
+}
+
 // Block-wide sum of one double per thread: wave shuffles, then the wave
 // partials added in wave order by every thread (deterministic, 2 barriers).
 __device__ double block_sum(double v, double *red) {
@@ -203,7 +265,7 @@ __global__ void __launch_bounds__(1024) k_chol_inv(const cd *__restrict__ G, int
 // ---- Hermitian eigensolver ---------------------------------------------------
 // Five stages on the stream:
 //   reduction  A = Q T Q^H, T real tridiagonal (lower Householder):
-//              k_hetrd_la (1 workgroup, n <= 192) or k_trd_apply + k_trd_step
+//              k_hetrd_la (1 workgroup, n <= 192) or k_trd_col (a launch per column)
 //   k_stebz    (k groups)      lowest k eigenvalues of T by 256-point multisection
 //   k_stein_w  (k waves)       eigenvectors of T by inverse iteration, in registers
 //   k_orth_chol2 / k_orth_chol / k_orth (1 workgroup), k_orth_clusters  re-orthogonalisation
@@ -211,22 +273,44 @@ __global__ void __launch_bounds__(1024) k_chol_inv(const cd *__restrict__ G, int
 //
 // ---- multi-workgroup reduction for n > 192 (the final Rayleigh-Ritz) --------
 // H_j = I - tau_j v_j v_j^H, A <- H_j^H A H_j, w = tau y - (|tau|^2 / 2)
-// Re(v^H y) v, A -= w v^H + v w^H, both triangles of the trailing square kept;
-// one column step is two launches:
-//   k_trd_apply (many workgroups): on the trailing square [j+1, n)^2 apply the
-//     pending rank-2 update of step j-1 and accumulate y = A v_j; a workgroup
-//     owns 64 rows (one per lane) and 64 columns (16 per wave), so every
-//     partial of y is a plain per-lane sum; partials go to ypart[chunk][row].
-//   k_trd_step (one workgroup): y = sum of the chunk partials (fixed order),
-//     w_j = tau y - (|tau|^2 / 2) Re(v^H y) v, the pivot column j+1 with the
-//     update of step j applied on the fly, d_{j+1}, and the reflector j+1
-//     (stored below the subdiagonal of column j+1, beta on the subdiagonal).
-// v of consecutive steps alternates between two buffers; rows outside a
-// reflector's range are zero in its buffer.
+// Re(v^H y) v, A -= w v^H + v w^H, both triangles of the trailing square kept.
+// One launch per column (k_trd_col): a column is a serial chain of two
+// reductions over the chip, bound by launch and memory latency, not by the
+// bytes (a 512^2 matrix is 4 MB).  Launch j
+//   - every workgroup by itself: y_{j-1} = sum of the chunk partials (fixed
+//     order, so all workgroups get the same bits), w_{j-1}, the pivot column j
+//     with the update of step j - 1 on the fly, d_j and the reflector v_j; one
+//     thread per row (n <= 1024);
+//   - then on its tile of TR rows x 128 columns of the trailing square
+//     [j + 1, n)^2, loaded at the start behind the vectors: the update of step
+//     j - 1 and the partial of A v_j over the tile's columns.
+// Repeating the vector work in every workgroup (its loads: 64 KB at n = 512)
+// costs less than the launch and the round trip through memory that a kernel
+// of its own takes: 13.0 us per column with the vector work in a kernel of one
+// workgroup, 4.4 us so (mean over n = 512; 7.4 -> 3.0 ms for the whole
+// eigensolve without its vectors).  Of these about 1 us each are the launch and
+// the loads; the rest is the serial chain of the two sums.
+// Threads: one per row left (256, 512 or 1024), since waves without rows only
+// delay the others' scalar work.  Tile rows: the fewest for which the repeated
+// vector loads don't show.  Measured on 193 / 256 / 512 / 1024 columns, whole
+// eigensolve with few vectors: 1.06 / 1.40 / 2.96 / 8.3 ms with 4, 8 and 32 rows
+// at 256, 512 and 1024 threads; 16 rows at 512 threads 3.1 ms, 32 rows 3.2 ms;
+// 16 rows at 1024 threads 9.2 ms, 8 rows 11.2 ms.
+// (n <= 192 keeps its single-workgroup form: about as fast at n = 192, one launch
+// instead of 192, and one CU instead of the chip while other contexts solve.)
+// Tiles lie on a fixed grid and are numbered in shells of 128 x 128 blocks from
+// the bottom right corner, so that the live ones are a prefix and a tile keeps
+// its workgroup number, hence its XCD and L2, for the whole reduction.
+// v and the partials alternate between two buffers (a launch reads the last
+// one's and writes its own); v is zero outside the reflector's rows.  Column
+// j - 1 of A receives its reflector in launch j: in launch j - 1 every
+// workgroup still reads that column.
+constexpr int kTrCols = 128;
+constexpr int kTrR256 = 4, kTrR512 = 8, kTrR1024 = 32;
+
 struct TrdState {
     cd *v[2];      // [n] reflectors of even / odd steps
-    cd *w;         // [n] w of the last step
-    cd *ypart;     // [nchunk][n]
+    cd *yp[2];     // [nblocks][n] partials of A v over 128 columns
 };
 
 __global__ void k_herm_sym(cd *__restrict__ A, int64_t lda, int n) {
@@ -243,158 +327,158 @@ __global__ void k_herm_sym(cd *__restrict__ A, int64_t lda, int n) {
     }
 }
 
-__global__ void __launch_bounds__(256)
-    k_trd_apply(cd *__restrict__ A, int64_t lda, int n, int j, TrdState S) {
-    __shared__ cd cvp[64], cwp[64], cv[64];
-    __shared__ cd yw[4][64];
-    const int r0 = j + 1;
-    const int L = n - r0;
-    const int nrb = (L + 63) / 64;
-    const int rb = blockIdx.x % nrb, cc = blockIdx.x / nrb;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const cd *vp = S.v[(j + 1) & 1];   // v_{j-1} (zero for j = 0)
-    const cd *v = S.v[j & 1];
-    const cd *wp = S.w;                // w_{j-1} (zero for j = 0)
-    const int c0 = r0 + 64 * cc;
-    if (threadIdx.x < 64) {
-        const int c = c0 + threadIdx.x;
-        const bool ok = c < n;
-        cvp[threadIdx.x] = ok ? vp[c] : cd{0.0, 0.0};
-        cwp[threadIdx.x] = ok ? wp[c] : cd{0.0, 0.0};
-        cv[threadIdx.x] = ok ? v[c] : cd{0.0, 0.0};
+template <int NT, int TR>
+__global__ void __launch_bounds__(NT)
+    k_trd_col(cd *__restrict__ A, int64_t lda, int n, int j, TrdState S, double *__restrict__ dd,
+              double *__restrict__ ee, cd *__restrict__ tau_out) {
+    // a wave's load covers TR rows x CS columns, a wave of the tile CS NQ columns
+    constexpr int NW = NT / 64, CS = 64 / TR, NQ = kTrCols / (CS * NW), NB = NT / kTrCols;
+    __shared__ cd svp[NT], sw[NT], sv[NT];   // v_{j-1}, w_{j-1}, v_j (from row r0)
+    __shared__ cd yw[NW][64];
+    __shared__ double red[2][NW];
+    __shared__ cd s_y, s_v, s_alpha;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const bool first = blockIdx.x == 0;
+    // this workgroup's tile
+    const int nb = (n + kTrCols - 1) / kTrCols;
+    const int q = blockIdx.x / (kTrCols / TR), sub = blockIdx.x % (kTrCols / TR);
+    int s = 0;
+    while ((s + 1) * (s + 1) <= q) ++s;
+    const int rs = q - s * s;
+    const int br = nb - 1 - (rs <= s ? s : rs - s - 1), bc = nb - 1 - (rs <= s ? rs : s);
+    const int i0 = kTrCols * br + TR * sub, c0 = kTrCols * bc;
+    if (!first && (i0 >= n || i0 + TR - 1 <= j)) return;   // no live row
+    const int kb = j / kTrCols, r0 = kTrCols * kb, row = r0 + t;   // this thread's row
+    // loads: the vectors first, the tile behind them
+    const bool in = row >= j && row < n;
+    cd yq[NB], vi = {0.0, 0.0}, c = {0.0, 0.0}, tau1 = {0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < NB; ++k) yq[k] = cd{0.0, 0.0};
+    double beta1 = 0.0;
+    if (j > 0) {
+        tau1 = tau_out[j - 1];
+        beta1 = ee[j - 1];
+        const cd *yp = S.yp[(j - 1) & 1];
+        if (in) vi = S.v[(j - 1) & 1][row];
+#pragma unroll
+        for (int k = 0; k < NB; ++k)
+            if (in && kb + k < nb) yq[k] = yp[(int64_t)(kb + k) * n + row];
+    }
+    if (in) c = A[(int64_t)j * lda + row];
+    const int i = i0 + lane % TR, cw = c0 + CS * NQ * wave + lane / TR;
+    const bool rok = i > j && i < n;
+    cd a[NQ];
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) {
+        const int col = cw + CS * k;
+        a[k] = rok && col > j && col < n ? A[(int64_t)col * lda + i] : cd{0.0, 0.0};
+    }
+    // w_{j-1} and column j
+#pragma unroll
+    for (int h = 1; h < NB; h *= 2)   // pairwise: fixed order, short chain
+#pragma unroll
+        for (int k = 0; k + h < NB; k += 2 * h) {
+            yq[k].x += yq[k + h].x;
+            yq[k].y += yq[k + h].y;
+        }
+    const cd y = yq[0];
+    const double vy = wave_total(vi.x * y.x + vi.y * y.y);
+    if (lane == 0) red[0][wave] = vy;
+    if (row == j) {
+        s_y = y;
+        s_v = vi;
     }
     __syncthreads();
-    const int i = r0 + 64 * rb + lane;
-    const bool rowok = i < n;
-    const cd vpi = rowok ? vp[i] : cd{0.0, 0.0}, wpi = rowok ? wp[i] : cd{0.0, 0.0};
-    double yr = 0.0, yi = 0.0;
-    if (rowok) {
-#pragma unroll 4
-        for (int q = 16 * wave; q < 16 * wave + 16; ++q) {
-            const int c = c0 + q;
-            if (c >= n) break;
-            cd a = A[(int64_t)c * lda + i];
-            const cd u1 = cmulz(wpi, cconj(cvp[q])), u2 = cmulz(vpi, cconj(cwp[q]));
-            a.x -= u1.x + u2.x;
-            a.y -= u1.y + u2.y;
-            A[(int64_t)c * lda + i] = a;
-            const cd vc = cv[q];
-            yr += a.x * vc.x - a.y * vc.y;
-            yi += a.x * vc.y + a.y * vc.x;
-        }
-    }
-    yw[wave][lane] = cd{yr, yi};
-    __syncthreads();
-    if (wave == 0 && rowok) {
-        const double sr = ((yw[0][lane].x + yw[1][lane].x) + yw[2][lane].x) + yw[3][lane].x;
-        const double si = ((yw[0][lane].y + yw[1][lane].y) + yw[2][lane].y) + yw[3][lane].y;
-        S.ypart[(int64_t)cc * n + i] = cd{sr, si};
-    }
-}
-
-// j = -1: no previous step (w = 0), pivot column 0 as stored
-__global__ void __launch_bounds__(1024)
-    k_trd_step(cd *__restrict__ A, int64_t lda, int n, int j, TrdState S, double *__restrict__ dd,
-               double *__restrict__ ee, cd *__restrict__ tau_out) {
-    __shared__ double red[16];
-    __shared__ cd s_y[1024], s_wl[1024];   // y and w of this step (n <= 1024)
-    __shared__ cd s_tau, s_scale;
-    __shared__ double s_beta;
-    const int t = threadIdx.x, nt = blockDim.x;
-    const int p = j + 1;   // pivot column of the next reflector
-    cd *v = S.v[j & 1];    // v_j (unused for j = -1)
-    cd *vn = S.v[p & 1];   // receives v_{j+1}
-    if (j >= 0) {
-        const int L = n - p, nch = (L + 63) / 64;
-        const cd tau = tau_out[j];
-        double part = 0.0;
-        for (int i = p + t; i < n; i += nt) {
-            double sr = 0.0, si = 0.0;
-            for (int q = 0; q < nch; ++q) {
-                const cd y = S.ypart[(int64_t)q * n + i];
-                sr += y.x;
-                si += y.y;
-            }
-            s_y[i] = cd{sr, si};
-            const cd vi = v[i];
-            part += vi.x * sr + vi.y * si;
-        }
-        const double vhy = block_sum(part, red);
-        const double nu = 0.5 * (tau.x * tau.x + tau.y * tau.y) * vhy;
-        for (int i = t; i < n; i += nt) {
-            cd wi = {0.0, 0.0};
-            if (i >= p) {
-                const cd y = s_y[i], vi = v[i];
-                const cd ty = cmulz(tau, y);
-                wi = cd{ty.x - nu * vi.x, ty.y - nu * vi.y};
-            }
-            S.w[i] = wi;
-            s_wl[i] = wi;
-        }
-        __syncthreads();
-    } else {
-        for (int i = t; i < n; i += nt) {
-            S.w[i] = cd{0.0, 0.0};
-            s_wl[i] = cd{0.0, 0.0};
-        }
-        __syncthreads();
-    }
-    // pivot column p with the update of step j: A(i, p) - v_i conj(w_p) - w_i conj(v_p)
-    const cd w1 = s_wl[p];
-    const cd v1 = j >= 0 ? v[p] : cd{0.0, 0.0};
-    auto col = [&](int i) -> cd {
-        cd a = A[(int64_t)p * lda + i];
-        if (j >= 0) {
-            const cd vi = v[i], wi = s_wl[i];
-            const cd u1 = cmulz(vi, cconj(w1)), u2 = cmulz(wi, cconj(v1));
-            a.x -= u1.x + u2.x;
-            a.y -= u1.y + u2.y;
-        }
-        return a;
+    auto total = [&](const double *r) {   // pairwise over the waves
+        double x = r[lane % NW];
+        x += dpp_mov<0xB1>(x);
+        x += dpp_mov<0x4E>(x);
+        if (NW > 4) x += dpp_mov<0x141>(x);
+        if (NW > 8) x += dpp_mov<0x140>(x);
+        return x;
     };
-    if (t == 0) dd[p] = col(p).x;
-    if (p == n - 1) return;
-    double part = 0.0;
-    for (int i = p + 2 + t; i < n; i += nt) {
-        const cd a = col(i);
-        part += a.x * a.x + a.y * a.y;
+    const double nu = 0.5 * (tau1.x * tau1.x + tau1.y * tau1.y) * total(red[0]);
+    const cd ty = cmulz(tau1, y), typ = cmulz(tau1, s_y), vj = s_v;
+    const cd w = {ty.x - nu * vi.x, ty.y - nu * vi.y};
+    const cd wj = {typ.x - nu * vj.x, typ.y - nu * vj.y};
+    if (j > 0) {
+        const cd u1 = cmulz(vi, cconj(wj)), u2 = cmulz(w, cconj(vj));
+        c.x -= u1.x + u2.x;
+        c.y -= u1.y + u2.y;
     }
-    const double sigma = block_sum(part, red);
-    if (t == 0) {
-        const cd alpha = col(p + 1);
-        if (sigma == 0.0 && alpha.y == 0.0) {
-            s_tau = cd{0.0, 0.0};
-            s_beta = alpha.x;
-            s_scale = cd{0.0, 0.0};
-        } else {
-            const double nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + sigma);
-            const double beta = alpha.x >= 0.0 ? -nrm : nrm;
-            const double dr = alpha.x - beta, di = alpha.y;
-            const double ib = 1.0 / beta, iden = 1.0 / (dr * dr + di * di);
-            s_tau = cd{-dr * ib, -alpha.y * ib};
-            s_scale = cd{dr * iden, -di * iden};
-            s_beta = beta;
+    if (first) {
+        if (row == j) dd[j] = c.x;
+        if (j > 0) {
+            if (row > j && in) A[(int64_t)(j - 1) * lda + row] = vi;   // kept for the back-transform
+            if (row == j) A[(int64_t)(j - 1) * lda + j] = cd{beta1, 0.0};
+        }
+    }
+    if (j == n - 1) return;
+    // reflector j
+    const double cc = wave_total(row > j + 1 ? c.x * c.x + c.y * c.y : 0.0);
+    if (lane == 0) red[1][wave] = cc;
+    if (row == j + 1) s_alpha = c;
+    __syncthreads();
+    const double sigma = total(red[1]);
+    const cd alpha = s_alpha;
+    cd tau = {0.0, 0.0}, scale = {0.0, 0.0};
+    double beta = alpha.x;
+    const bool reflect = !(sigma == 0.0 && alpha.y == 0.0);
+    if (reflect) {
+        const double nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + sigma);
+        beta = alpha.x >= 0.0 ? -nrm : nrm;
+        const double dr = alpha.x - beta, di = alpha.y;
+        const double ib = rcp_nr(beta), iden = rcp_nr(dr * dr + di * di);
+        tau = cd{-dr * ib, -di * ib};
+        scale = cd{dr * iden, -di * iden};
+    }
+    cd v = {0.0, 0.0};
+    if (reflect && row == j + 1) v = cd{1.0, 0.0};
+    else if (reflect && row > j + 1 && row < n) v = cmulz(c, scale);
+    svp[t] = vi;
+    sw[t] = w;
+    sv[t] = v;
+    if (first) {
+        if (in) S.v[j & 1][row] = v;
+        if (t == 0) {
+            tau_out[j] = tau;
+            ee[j] = beta;
         }
     }
     __syncthreads();
-    const cd tau = s_tau, scale = s_scale;
-    const bool reflect = !(tau.x == 0.0 && tau.y == 0.0);
-    for (int i = t; i < n; i += nt) {
-        cd vv = {0.0, 0.0};
-        if (reflect && i == p + 1) vv = cd{1.0, 0.0};
-        else if (reflect && i > p + 1) vv = cmulz(col(i), scale);
-        vn[i] = vv;
-        if (i > p + 1) A[(int64_t)p * lda + i] = vv;   // reflector kept for the back-transform
+    // the tile: update of step j - 1, partial of A v_j
+    const cd vpi = svp[i - r0], wpi = sw[i - r0];
+    cd acc = {0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) {
+        const int col = cw + CS * k;
+        const cd u1 = cmulz(wpi, cconj(svp[col - r0])), u2 = cmulz(vpi, cconj(sw[col - r0])), vc = sv[col - r0];
+        a[k].x -= u1.x + u2.x;
+        a[k].y -= u1.y + u2.y;
+        if (rok && col > j && col < n) A[(int64_t)col * lda + i] = a[k];
+        acc.x += a[k].x * vc.x - a[k].y * vc.y;
+        acc.y += a[k].x * vc.y + a[k].y * vc.x;
     }
-    if (t == 0) {
-        tau_out[p] = tau;
-        ee[p] = s_beta;
-        A[(int64_t)p * lda + p + 1] = cd{s_beta, 0.0};
+    yw[wave][lane] = acc;
+    __syncthreads();
+    if (wave == 0) {   // the waves' partials in pairs, then the CS lanes of a row
+        cd x[NW];
+#pragma unroll
+        for (int k = 0; k < NW; ++k) x[k] = yw[k][lane];
+#pragma unroll
+        for (int h = 1; h < NW; h *= 2)
+#pragma unroll
+            for (int k = 0; k + h < NW; k += 2 * h) {
+                x[k].x += x[k + h].x;
+                x[k].y += x[k + h].y;
+            }
+        const cd sum = {stride_sum<TR>(x[0].x), stride_sum<TR>(x[0].y)};
+        if (lane < TR && rok) S.yp[j & 1][(int64_t)bc * n + i] = sum;
     }
 }
 
 // ---- register-resident reduction for n <= 32 T (T <= 6) ----------------------
-// The same Householder sequence as k_trd_apply / k_trd_step, but the whole
+// The same Householder sequence as k_trd_col, but the whole
 // matrix stays in registers: 1024 threads on a 32 x 32 grid, each holding one
 // element of every tile b <= a (off-diagonal tiles are stored once and used
 // for both triangles of y = A v; diagonal tiles are stored in full).  Tiles
@@ -408,54 +492,6 @@ __device__ __forceinline__ void unroll_for(F &&f) {
         f(std::integral_constant<int, B>{});
         unroll_for<B + 1, E>(static_cast<F &&>(f));
     }
-}
-
-template <int CTRL>
-__device__ __forceinline__ double dpp_mov(double x) {
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xF, 0xF, true);
-    return __hiloint2double(hi, lo);
-}
-template <int CTRL>
-__device__ __forceinline__ float dpp_mov(float x) {   // one 32-bit move
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
-}
-// sum over the 16 lanes of a DPP row; every lane of the row gets the same value
-template <class R>
-__device__ __forceinline__ R row16_sum(R x) {
-    x += dpp_mov<0xB1>(x);    // quad_perm [1,0,3,2]
-    x += dpp_mov<0x4E>(x);    // quad_perm [2,3,0,1]
-    x += dpp_mov<0x141>(x);   // row_half_mirror
-    x += dpp_mov<0x140>(x);   // row_mirror
-    return x;
-}
-template <class R>
-__device__ __forceinline__ R quad_sum(R x) {
-    x += dpp_mov<0xB1>(x);
-    x += dpp_mov<0x4E>(x);
-    return x;
-}
-// lanes whose DPP row is disabled by ROW_MASK read 0
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_rows(double x) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROW_MASK, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROW_MASK, 0xF, false);
-    return __hiloint2double(hi, lo);
-}
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ float dpp_rows(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, ROW_MASK, 0xF, false));
-}
-// Wave sum returned as a wave-uniform value, without LDS: the row sums, then
-// row_bcast:15 adds row 0 into row 1 and row 2 into row 3, row_bcast:31 adds
-// rows 0 + 1 into rows 2 and 3, and lane 63 holds the total (same order of
-// additions in every wave).
-template <class R>
-__device__ __forceinline__ R wave_total(R x) {
-    x = row16_sum(x);
-    x += dpp_rows<0x142, 0xA>(x);   // row_bcast:15
-    x += dpp_rows<0x143, 0xC>(x);   // row_bcast:31
-    return lane_read(x, 63);
 }
 
 // Look-ahead form of the register-resident reduction (same Householder
@@ -1428,7 +1464,7 @@ void launch_chol_inv_f64(const cd *G, int64_t ldg, int n, cd *Rinv, int64_t ldr,
 size_t heev_scratch_bytes(int n, int k) {
     const size_t nch = (size_t)(n + 63) / 64;
     return 8 * 256 + (size_t)n * 16 + 2 * (size_t)n * 8 + (size_t)n * k * 8 +
-           (3 + nch) * (size_t)n * 16;   // reflector pair, w and the y partials (n > 192)
+           (3 + nch) * (size_t)n * 16;   // n > 192: reflector pair and two sets of ceil(n / 128) partials
 }
 
 void launch_heev_f64(cd *A, int64_t lda, int n, int k, double *w, cd *V, int64_t ldv, void *scratch,
@@ -1468,18 +1504,25 @@ void launch_heev_f64(cd *A, int64_t lda, int n, int k, double *w, cd *V, int64_t
         p += align((size_t)n * 16);
         S.v[1] = reinterpret_cast<cd *>(p);
         p += align((size_t)n * 16);
-        S.w = reinterpret_cast<cd *>(p);
-        p += align((size_t)n * 16);
-        S.ypart = reinterpret_cast<cd *>(p);
+        const int nb = (n + kTrCols - 1) / kTrCols;
+        S.yp[0] = reinterpret_cast<cd *>(p);
+        S.yp[1] = S.yp[0] + (size_t)nb * n;
         hipLaunchKernelGGL(k_herm_sym, dim3((unsigned)(((int64_t)n * n + 255) / 256)), dim3(256), 0, st, A, lda,
                            n);
-        launch_zero(S.v[0], n, n, 1, st);
-        launch_zero(S.v[1], n, n, 1, st);
-        hipLaunchKernelGGL(k_trd_step, dim3(1), dim3(1024), 0, st, A, lda, n, -1, S, d, e, tau);
-        for (int j = 0; j + 1 < n; ++j) {
-            const int L = n - 1 - j, nb = (L + 63) / 64;
-            hipLaunchKernelGGL(k_trd_apply, dim3(nb * nb), dim3(256), 0, st, A, lda, n, j, S);
-            hipLaunchKernelGGL(k_trd_step, dim3(1), dim3(1024), 0, st, A, lda, n, j, S, d, e, tau);
+        for (int j = 0; j < n; ++j) {
+            const int live = std::max(1, nb - (j + 1) / kTrCols);   // blocks of 128 rows or columns
+            auto col = [&](auto nt, auto tr) {
+                constexpr int NT = decltype(nt)::value, TR = decltype(tr)::value;
+                hipLaunchKernelGGL((k_trd_col<NT, TR>), dim3(live * live * (kTrCols / TR)), dim3(NT), 0, st, A, lda,
+                                   n, j, S, d, e, tau);
+            };
+            const int rows = kTrCols * (nb - j / kTrCols);   // rows of the kernel, one per thread
+            if (rows <= 256)
+                col(std::integral_constant<int, 256>{}, std::integral_constant<int, kTrR256>{});
+            else if (rows <= 512)
+                col(std::integral_constant<int, 512>{}, std::integral_constant<int, kTrR512>{});
+            else
+                col(std::integral_constant<int, 1024>{}, std::integral_constant<int, kTrR1024>{});
         }
     }
     // 2. eigenvalues, one workgroup each, spread over k CUs
