@@ -32,6 +32,14 @@ __device__ __forceinline__ double rcp_nr(double d) {
     return r;
 }
 
+// d^-1/2: the hardware value refined by two Newton steps (d positive and normal)
+__device__ __forceinline__ double rsqrt_nr(double d) {
+    double r = __builtin_amdgcn_rsq(d);
+    r = fma(0.5 * r, fma(-d * r, r, 1.0), r);
+    r = fma(0.5 * r, fma(-d * r, r, 1.0), r);
+    return r;
+}
+
 // FP32: the hardware reciprocal (within 1 ulp) and square root
 __device__ __forceinline__ float rcp_nr(float d) { return __builtin_amdgcn_rcpf(d); }
 __device__ __forceinline__ double sqrt_r(double x) { return sqrt(x); }
@@ -121,145 +129,189 @@ __device__ double block_sum(double v, double *red) {
     return s;
 }
 
-// ---- Cholesky + inverse of the factor (n <= 64, in registers) -----------------
+template <int B, int E, class F>
+__device__ __forceinline__ void unroll_for(F &&f) {
+    if constexpr (B < E) {
+        f(std::integral_constant<int, B>{});
+        unroll_for<B + 1, E>(static_cast<F &&>(f));
+    }
+}
+
+// ---- Cholesky + inverse of the factor (n <= 64) --------------------------------
 // Gaussian elimination without pivoting on the augmented matrix [G | I]: the
 // row operations that reduce G (Hermitian positive definite, G = L D L^H) to
 // the upper triangle D L^H turn I into L^-1; scaling row j of both by d_j^-1/2
-// gives [R | R^-H] with G = R^H R.  Step j subtracts conj(g_ja) / d_j times the
-// (unscaled) pivot row from every row a > j, so the only communication is the
-// pivot row, broadcast through LDS (double buffered: one barrier per step);
-// rows stay unscaled (the augmented half ends as L^-1) and are scaled by
-// d_a^-1/2 at the end.  1024 threads as a 32 x 32 grid; thread (ti, tj) holds the 2 x 2 tiles rows
-// 2 ti .., columns 2 tj .. of G (upper part used) and of the augmented half.
-// A wave covers rows 4w .. 4w + 3 and stops updating once they are all
-// eliminated; waves of each SIMD cover rows spread over the matrix, so the
-// work per SIMD shrinks with the step.  Rows and columns >= n are padded with
-// the identity (inert pivots).
+// gives [R | R^-H] with G = R^H R.  Rows and columns >= n are padded with the
+// identity.
+// Bound by the chain of n pivots (reciprocal, multiplier, next pivot: about
+// 250 cycles each), so 16 pivots at a time are eliminated inside a wave, without
+// a barrier.  A panel is 16 rows of the augmented matrix, 16 + 64 columns: the
+// diagonal block and, for each of the four column blocks i, the block of G
+// right of it (i > k), of the inverse left of it (i < k), or the identity
+// (i = k).  Waves 0 and 1 each hold the diagonal block, one column per lane in
+// lanes 0-15, and half of the 64 others in lanes 16-47; the pivot row's entries
+// in lanes j and a > j are the pivot and the multipliers, read as scalars.
+// The blocks of the later panels stay in the matrix cores' accumulators: wave
+// 2 + i holds column block i of panels 1-3, which receive
+// M(c, i) -= R(k, c)^H M(k, i) after panel k; the four blocks of the next panel do so
+// ahead of it, one on each SIMD, the others beside it.
+// Measured at n = 16 / 64: 6.6 / 23.8 us (12.7 / 47.7 us with a pair of pivots per
+// barrier on a 32 x 32 grid of threads).  About 470 cycles per pivot, of them
+// 250 the chain; 6 waves, so that the panel's registers don't spill (14 waves
+// with one block each: 33 us).
 constexpr int kCholMax = 64;
+constexpr int kCholP = 16;   // rows of a panel
+constexpr int kCholWaves = 6;
 
-__global__ void __launch_bounds__(1024) k_chol_inv(const cd *__restrict__ G, int64_t ldg, int n,
-                                                   cd *__restrict__ Rinv, int64_t ldr, int *status) {
-    // pivot rows j, j + 1 of a pair step, double buffered: [buffer][row of the pair][column]
-    __shared__ cd pg[2][2][kCholMax];   // G part (columns >= j meaningful)
-    __shared__ cd pu[2][2][kCholMax];   // augmented part (columns <= j + 1 meaningful)
-    __shared__ double diag[kCholMax];
-    const int t = threadIdx.x, ti = t >> 5, tj = t & 31;
-    const int a0 = 2 * ti, b0 = 2 * tj;         // rows a0, a0 + 1 form one pivot pair
-    const int wrow_last = 4 * (t >> 6) + 3;   // last row of this wave
-    cd g[2][2], u[2][2];
+int chol_panels(int n) { return (n + kCholP - 1) / kCholP; }
+// row block, then the staged G, later reused for the other two row blocks
+size_t chol_lds(int n) {
+    const size_t N = kCholP * (size_t)chol_panels(n), block = kCholP * kCholMax;
+    return (block + std::max(N * (N + 1), N > kCholP ? 2 * block : 0)) * 16;
+}
+
+__global__ void __launch_bounds__(64 * kCholWaves) k_chol_inv(const cd *__restrict__ G, int64_t ldg, int n,
+                                                      cd *__restrict__ Rinv, int64_t ldr, int *status) {
+    extern __shared__ double chol_smem[];
+    typedef double v4 __attribute__((ext_vector_type(4)));
+    constexpr int P = kCholP, W = kCholMax;
+    const int np = (n + P - 1) / P, N = P * np, LS = N + 1;
+    cd *const out0 = reinterpret_cast<cd *>(chol_smem);   // panels 0, 2: [16][64]
+    cd *const sg = out0 + P * W;                          // G as stored, [column][LS]
+    cd *const in = sg, *const out1 = sg + P * W;          // next panel; panel 1
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    if (lane < N) {
+        constexpr int Q = (W + kCholWaves - 1) / kCholWaves;
+        cd x[Q];
 #pragma unroll
-    for (int ia = 0; ia < 2; ++ia)
-#pragma unroll
-        for (int ib = 0; ib < 2; ++ib) {
-            const int a = a0 + ia, b = b0 + ib;
-            cd v = {a == b ? 1.0 : 0.0, 0.0};
-            if (a < n && b < n) {   // Hermitian part of the stored Gram
-                const cd x = G[(int64_t)b * ldg + a], y = G[(int64_t)a * ldg + b];
-                v = cd{0.5 * (x.x + y.x), 0.5 * (x.y - y.y)};
-                if (a == b) v.y = 0.0;
-            }
-            g[ia][ib] = v;
-            u[ia][ib] = cd{a == b ? 1.0 : 0.0, 0.0};
-            if (a == b) diag[a] = v.x;
-            if (ti == 0) {
-                pg[0][ia][b] = v;
-                pu[0][ia][b] = u[ia][ib];
-            }
+        for (int q = 0; q < Q; ++q) {
+            const int b = wave + kCholWaves * q;
+            x[q] = lane < n && b < n ? G[(int64_t)b * ldg + lane] : cd{lane == b ? 1.0 : 0.0, 0.0};
         }
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (wave + kCholWaves * q < N) sg[(wave + kCholWaves * q) * LS + lane] = x[q];
+    }
     __syncthreads();
-    double dmax = 0.0;
-    for (int i = 0; i < n; ++i) dmax = fmax(dmax, diag[i]);
+    double dmax = lane < n ? fmax(sg[lane * LS + lane].x, 0.0) : 0.0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) dmax = fmax(dmax, __shfl_xor(dmax, o));
     // a tiny diagonal shift keeps a numerically semi-definite Gram factorable
     const double shift = 1e-15 * dmax * n;
-    bool fail = false;
-    double dpiv[2] = {1.0, 1.0};   // pivots of this thread's rows (rows stay unscaled)
-    // two pivots per barrier: every thread forms row j + 1 after pivot j itself
-    // from the two broadcast rows (row j + 1 arrives without pivot j applied)
-    for (int j = 0; j < n; j += 2) {
-        const int bsel = (j >> 1) & 1;
-        const cd *r0g = pg[bsel][0], *r1g = pg[bsel][1], *r0u = pu[bsel][0], *r1u = pu[bsel][1];
-        double d0 = r0g[j].x + shift;
-        if (!(d0 > 1e-300) || !isfinite(d0)) {
-            fail = true;
-            d0 = 1.0;
-        }
-        const double inv0 = rcp_nr(d0);
-        const cd c01 = r0g[j + 1];
-        const cd l = {c01.x * inv0, -c01.y * inv0};   // row j + 1 multiplier of pivot j
-        auto r1gp = [&](int c) {                       // row j + 1 of G after pivot j
-            const cd pr = cmulz(l, r0g[c]);
-            const cd v = r1g[c];
-            return cd{v.x - pr.x, v.y - pr.y};
-        };
-        double d1 = r1gp(j + 1).x + shift;
-        if (j + 1 < n && (!(d1 > 1e-300) || !isfinite(d1))) {
-            fail = true;
-            d1 = 1.0;
-        }
-        if (j + 1 >= n) d1 = 1.0;
+    auto herm = [&](int a, int b) {   // Hermitian part of the stored Gram, shifted
+        const cd x = sg[b * LS + a], y = sg[a * LS + b];
+        return cd{0.5 * (x.x + y.x) + (a == b ? shift : 0.0), 0.5 * (x.y - y.y)};
+    };
+    if (wave < 2) {
+        const bool diag = lane < P, other = !diag && lane < 3 * P;
+        const int o = 2 * P * wave + (lane - P) % (2 * P), slot = o / P;   // column of [inverse | G]
+        cd g[P];
+        {
+            const int col = diag ? lane : min(o, N - 1);
 #pragma unroll
-        for (int ia = 0; ia < 2; ++ia) {
-            if (a0 + ia == j) dpiv[ia] = d0;
-            if (a0 + ia == j + 1) dpiv[ia] = d1;
+            for (int r = 0; r < P; ++r) g[r] = herm(r, col);
         }
-        if (wrow_last > j) {   // rows below pivot j in this wave (uniform per wave)
-            const double inv1 = rcp_nr(d1);
-            cd m0[2], m1[2];
+        bool fail = false;
+        for (int k = 0;; ++k) {
+            int ln = lane;
+            asm volatile("" : "+v"(ln));   // keeps the masks of the lanes out of registers across panels
+            const int unit = !diag && slot == k ? ln % P : -1;   // this lane's row of the identity
 #pragma unroll
-            for (int ia = 0; ia < 2; ++ia) {
-                const int a = a0 + ia;
-                const cd p0 = r0g[a], p1 = r1gp(a);
-                m0[ia] = a > j ? cd{p0.x * inv0, -p0.y * inv0} : cd{0.0, 0.0};
-                m1[ia] = a > j + 1 ? cd{p1.x * inv1, -p1.y * inv1} : cd{0.0, 0.0};
+            for (int r = 0; r < P; ++r) {
+                g[r].x = unit < 0 ? g[r].x : unit == r ? 1.0 : 0.0;
+                g[r].y = unit < 0 ? g[r].y : 0.0;
             }
-            cd g0[2], g1[2], u0[2], u1[2];
+            double dp = 1.0;   // lane r: pivot of row r
+            auto pivot = [&](int j) {   // 1 / d_j
+                const double d = lane_read(g[j].x, j);
+                const bool bad = !(d > 1e-300) | !(d <= DBL_MAX);
+                fail |= bad;
+                dp = ln == j ? (bad ? 1.0 : d) : dp;
+                return bad ? 1.0 : rcp_nr(d);
+            };
+            double inv = pivot(0);
+            unroll_for<0, P>([&](auto j_) {
+                constexpr int j = j_;
+                if (P * k + j >= n) return;   // only padding left
+                const cd tj = {g[j].x * inv, g[j].y * inv};
+                // row a -= conj(g_ja) / d_j row j; the next pivot as soon as its row is there.
+                // Four rows at a time, or the multipliers of all rows spill
+                unroll_for<j + 1, P>([&](auto a_) {
+                    constexpr int a = a_;
+                    const double mr = lane_read(g[j].x, a), mi = lane_read(g[j].y, a);
+                    g[a].x = fma(-mi, tj.y, fma(-mr, tj.x, g[a].x));
+                    g[a].y = fma(mi, tj.x, fma(-mr, tj.y, g[a].y));
+                    if constexpr (a == j + 1) inv = pivot(a);
+                    if constexpr ((a - j) % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+                });
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            const double isd = rsqrt_nr(dp);
+            cd *const out = k & 1 ? out1 : out0;
 #pragma unroll
-            for (int ib = 0; ib < 2; ++ib) {
-                const int b = b0 + ib;
-                g0[ib] = r0g[b];
-                g1[ib] = r1gp(b);
-                u0[ib] = r0u[b];
-                const cd pr = cmulz(l, u0[ib]), v = r1u[b];
-                u1[ib] = cd{v.x - pr.x, v.y - pr.y};
+            for (int r = 0; r < P; ++r) {
+                const double sc = lane_read(isd, r);
+                g[r].x *= sc;
+                g[r].y *= sc;
+                if (other && k + 1 < np) out[r * W + o] = g[r];
             }
+            if (k + 1 < np) __syncthreads();
+            // R^-1 (upper) = (R^-H)^H with R^-H = D^-1/2 L^-1
+            cd *dst = Rinv + (int64_t)P * k * ldr + o;
 #pragma unroll
-            for (int ia = 0; ia < 2; ++ia)
-#pragma unroll
-                for (int ib = 0; ib < 2; ++ib) {
-                    const int a = a0 + ia, b = b0 + ib;
-                    if (b >= a) {
-                        const cd p0 = cmulz(m0[ia], g0[ib]), p1 = cmulz(m1[ia], g1[ib]);
-                        g[ia][ib].x -= p0.x + p1.x;
-                        g[ia][ib].y -= p0.y + p1.y;
-                    }
-                    const cd q0 = cmulz(m0[ia], u0[ib]), q1 = cmulz(m1[ia], u1[ib]);
-                    u[ia][ib].x -= q0.x + q1.x;
-                    u[ia][ib].y -= q0.y + q1.y;
-                }
-            // the next pair's rows (j + 2 after pivots <= j + 1, j + 3 likewise) to the other buffer
-            if (j + 2 < n && a0 == j + 2) {
-#pragma unroll
-                for (int ia = 0; ia < 2; ++ia)
-#pragma unroll
-                    for (int ib = 0; ib < 2; ++ib) {
-                        pg[bsel ^ 1][ia][b0 + ib] = g[ia][ib];
-                        pu[bsel ^ 1][ia][b0 + ib] = u[ia][ib];
-                    }
+            for (int r = 0; r < P; ++r) {
+                if (other && P * k + r < n && o < n) *dst = slot <= k ? cd{g[r].x, -g[r].y} : cd{0.0, 0.0};
+                dst += ldr;
             }
+            if (k + 1 == np) break;
+            __syncthreads();
+            const int src = diag ? P * (k + 1) + ln : o;
+#pragma unroll
+            for (int r = 0; r < P; ++r) g[r] = in[r * W + src];
         }
+        if (fail && t == 0) atomicOr(status, 1);
+        return;
+    }
+    // blocks (c, i) of the later panels; i < c: of the inverse (zero so far), else of G
+    const int i = wave - 2, li = lane & 15, gr = lane >> 4;
+    v4 re[3], im[3];
+    auto init = [&](auto c_) {
+        constexpr int c = c_;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const cd v = i >= c && i < np ? herm(P * c + gr + 4 * r, P * i + li) : cd{0.0, 0.0};
+            re[c - 1][r] = v.x;
+            im[c - 1][r] = v.y;
+        }
+    };
+    // M(c, i) -= R(k, c)^H M(k, i); the inverse's blocks i > k are still zero
+    auto update = [&](auto c_, auto k_) {
+        constexpr int c = c_, k = k_;
+        if (c >= np || i >= np || (i > k && i < c)) return;
+        const cd *const m = k & 1 ? out1 : out0;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int row = (4 * s + gr) * W;
+            const cd a = m[row + P * c + li], b = m[row + P * i + li];
+            re[c - 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.x, b.x, re[c - 1], 0, 0, 0);
+            im[c - 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.x, b.y, im[c - 1], 0, 0, 0);
+            re[c - 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.y, re[c - 1], 0, 0, 0);
+            im[c - 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.x, im[c - 1], 0, 0, 0);
+        }
+    };
+    unroll_for<1, 4>(init);
+    if (np > 1) __syncthreads();   // panel 0 done
+    unroll_for<1, 4>([&](auto k_) {
+        constexpr int k = k_;
+        if (k >= np) return;
+        std::integral_constant<int, k - 1> last;
+        update(k_, last);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) in[(gr + 4 * r) * W + P * i + li] = cd{re[k - 1][r], im[k - 1][r]};
         __syncthreads();
-    }
-    // R^-1 (upper) = (R^-H)^H with R^-H = D^-1/2 L^-1
-#pragma unroll
-    for (int ia = 0; ia < 2; ++ia) {
-        const double isd = 1.0 / sqrt(dpiv[ia]);
-#pragma unroll
-        for (int ib = 0; ib < 2; ++ib) {
-            const int a = a0 + ia, c = b0 + ib;
-            if (a < n && c < n) Rinv[(int64_t)a * ldr + c] = cd{u[ia][ib].x * isd, -u[ia][ib].y * isd};
-        }
-    }
-    if (fail && t == 0) atomicOr(status, 1);
+        unroll_for<k + 1, 4>([&](auto c_) { update(c_, last); });
+        if (k + 1 < np) __syncthreads();
+    });
 }
 
 // ---- Hermitian eigensolver ---------------------------------------------------
@@ -485,14 +537,6 @@ __global__ void __launch_bounds__(NT)
 // whose rows or columns are all finished are skipped.  All sums run in a fixed
 // order (deterministic).  The kernel is k_hetrd_la below.
 constexpr int kRfMaxT = 6;
-
-template <int B, int E, class F>
-__device__ __forceinline__ void unroll_for(F &&f) {
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        unroll_for<B + 1, E>(static_cast<F &&>(f));
-    }
-}
 
 // Look-ahead form of the register-resident reduction (same Householder
 // sequence and storage of the reflectors): thread (ti, tj) = (t % 32, t / 32)
@@ -1457,7 +1501,9 @@ __global__ void __launch_bounds__(64) k_unmtr_w(const cd *__restrict__ A, int64_
 void launch_chol_inv_f64(const cd *G, int64_t ldg, int n, cd *Rinv, int64_t ldr, int *status,
                          hipStream_t st) {
     PW_REQUIRE(n >= 1 && n <= kCholMax, PW_ERR_ARG, "block size must be in [1, 64]");
-    hipLaunchKernelGGL(k_chol_inv, dim3(1), dim3(1024), 0, st, G, ldg, n, Rinv, ldr, status);
+    const size_t sm = chol_lds(n);
+    ensure_smem_limit((const void *)k_chol_inv, sm);
+    hipLaunchKernelGGL(k_chol_inv, dim3(1), dim3(64 * kCholWaves), sm, st, G, ldg, n, Rinv, ldr, status);
     PW_HIP(hipGetLastError());
 }
 
