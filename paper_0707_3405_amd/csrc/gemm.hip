@@ -98,6 +98,12 @@ __device__ __forceinline__ cpx<T> coef_keep(const cd &v, bool ok) {
     return cpx<T>{ok ? T(v.x) : T(0), ok ? T(v.y) : T(0)};
 }
 
+// element `bytes` past a uniform base
+template <class E>
+__device__ __forceinline__ const E &at_offset(const E *base, uint32_t bytes) {
+    return *reinterpret_cast<const E *>(reinterpret_cast<const char *>(base) + bytes);
+}
+
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -526,7 +532,20 @@ __global__ void __launch_bounds__(kThreads)
 // 494 so; complex64, whose 768 slots 4-block workgroups left unevenly filled,
 // 432 x 64 at K = 34208 95 us, 80 so.)  A loop over such ranges in one round
 // costs the FP64 kernel its accumulation registers (115 -> 123 us).
-// Same LDS staging and double buffering as k_gemm_nn_lds.
+// Same LDS staging and double buffering as k_gemm_nn_lds, but whole k-blocks are
+// loaded without a condition, from a uniform base and 32-bit lane offsets: rows
+// and columns past the operands only feed results that are not stored, so their
+// addresses are clamped and their values kept, and only k past p, in the last
+// block, has to be zero in both operands.  (A condition on every load costs a
+// wave branches and 64-bit addresses on each k-block; a coefficient matrix
+// whose offsets don't fit 30 bits takes the masked form throughout.)  A wave's
+// priority rises with its progress through the k-block and stays up while it
+// stages the next one: of the waves on a SIMD the furthest finishes first and
+// loads while the others multiply, instead of all of them waiting in step.
+// K = 34208: complex64 432 x 64 82 -> 73 us, 192 x 64 41 -> 37, FP64 432 x 64
+// 129 -> 126, 64 x 64 26.4 -> 27.1; 82592: complex64 748 x 64 303 -> 272, FP64
+// 494 -> 484; K = 11392: complex64 256 x 23 26.4 -> 23.2.  (k_gemm_tn_lds
+// measured 3-6 % slower with such loads, and 3-14 % with the priorities.)
 constexpr int kNnMaxRb = 5;
 template <class T>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 1 : 3)))
@@ -544,45 +563,54 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(s
     const int nrb = (int)(rb1 - rb0);   // 1 .. kNnMaxRb (host guarantees)
     const int64_t rbase = rb0 * 16;
     const int cbase = tn * kTile;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int li = lane & 15, gq = lane >> 4;
 
     // global -> LDS: A instruction (u, h) covers column kb + 4 wave + u, rows
     // 64 h + lane; C instruction u covers columns 16 wave + 4u + gq, k rows li
     const int nrows = 16 * nrb;
-    const bool arow0 = lane < nrows && rbase + lane < K;
-    const bool arow1 = 64 + lane < nrows && rbase + 64 + lane < K;
-    const cpx<T> *Arow0 = A + (arow0 ? rbase + lane : 0);
-    const cpx<T> *Arow1 = A + (arow1 ? rbase + 64 + lane : 0);
-    const cd *Cc[4];
-    bool cok[4];
+    const uint32_t va0 = (uint32_t)((lane < nrows && rbase + lane < K ? lane : 0) * sizeof(cpx<T>));
+    const uint32_t va1 = (uint32_t)((64 + lane < nrows && rbase + 64 + lane < K ? 64 + lane : 0) * sizeof(cpx<T>));
+    const bool upper = nrows > 64 && lane < NRW - 64;
+    const cd *const Ct = Cm + (int64_t)cbase * ldc;
+    const bool near = ldc < (int64_t)(1 << 30) / (int)(kTile * sizeof(cd));
+    uint32_t vc[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-        const int col = cbase + 16 * wave + 4 * u + gq;
-        cok[u] = col < q;
-        Cc[u] = Cm + (int64_t)(cok[u] ? col : 0) * ldc;
+        const int c = 16 * wave + 4 * u + gq;
+        vc[u] = (uint32_t)(((cbase + c < q ? c : 0) * (uint32_t)ldc + li) * sizeof(cd));
     }
     cpx<T> ra0[4], ra1[4];
-    cd rc[4];
-    auto gload = [&](int kb) {   // clamped addresses
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int kk = kb + 4 * wave + u;
-            const int64_t ko = (int64_t)(kk < p ? kk : 0) * lda;
-            ra0[u] = tile_load(Arow0 + ko, arow0 && kk < p);
-            ra1[u] = tile_load(Arow1 + ko, arow1 && kk < p);
-            const int kc = kb + li;
-            rc[u] = coef_load<T>(Cc[u] + (kc < p ? kc : 0), cok[u] && kc < p);
+    for (int u = 0; u < 4; ++u) ra1[u] = cpx<T>{T(0), T(0)};
+    cd rc[4];
+    auto gload = [&](int kb) {
+        if (near && kb + KB <= p) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                ra0[u] = at_offset(A + (int64_t)(kb + 4 * wave + u) * lda + rbase, va0);
+                rc[u] = at_offset(Ct + kb, vc[u]);
+            }
+            if (upper) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) ra1[u] = at_offset(A + (int64_t)(kb + 4 * wave + u) * lda + rbase, va1);
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int kk = kb + 4 * wave + u, c = 16 * wave + 4 * u + gq;
+                ra0[u] = kk < p ? at_offset(A + (int64_t)kk * lda + rbase, va0) : cpx<T>{T(0), T(0)};
+                ra1[u] = upper && kk < p ? at_offset(A + (int64_t)kk * lda + rbase, va1) : cpx<T>{T(0), T(0)};
+                rc[u] = kb + li < p && cbase + c < q ? Ct[(int64_t)c * ldc + kb + li] : cd{0.0, 0.0};
+            }
         }
     };
-    auto lstore = [&](int buf, int kb) {
+    auto lstore = [&](int buf) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int kk = kb + 4 * wave + u;
-            sA[buf][(4 * wave + u) * LDA + lane] = tile_keep(ra0[u], arow0 && kk < p);
-            if (lane < NRW - 64)
-                sA[buf][(4 * wave + u) * LDA + 64 + lane] = tile_keep(ra1[u], arow1 && kk < p);
-            sC[buf][(16 * wave + 4 * u + gq) * LDCC + li] = coef_keep<T>(rc[u], cok[u] && kb + li < p);
+            sA[buf][(4 * wave + u) * LDA + lane] = ra0[u];
+            if (upper) sA[buf][(4 * wave + u) * LDA + 64 + lane] = ra1[u];
+            sC[buf][(16 * wave + 4 * u + gq) * LDCC + li] = cpx<T>{T(rc[u].x), T(rc[u].y)};
         }
     };
     const bool colv = cbase + 16 * wave < q;   // this wave's 16 columns (uniform per wave)
@@ -602,6 +630,10 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(s
         auto mma = [&](int buf) {
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
+                s == 0   ? __builtin_amdgcn_s_setprio(0)
+                : s == 1 ? __builtin_amdgcn_s_setprio(1)
+                : s == 2 ? __builtin_amdgcn_s_setprio(2)
+                         : __builtin_amdgcn_s_setprio(3);
                 const cpx<T> b = sC[buf][(16 * wave + li) * LDCC + 4 * gq + s];
                 const T bs = b.x + b.y;
 #pragma unroll
@@ -616,16 +648,16 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(s
         };
         if (p > 0) {   // every wave stages its share of A, also when its columns are idle
             gload(0);
-            lstore(0, 0);
+            lstore(0);
         }
         __syncthreads();
         if (p > 0) {
             int buf = 0;
             for (int kb = 0; kb < p; kb += KB) {
                 const bool more = kb + KB < p;
-                gload(kb + KB);   // past p: clamped, never stored
+                gload(kb + KB);   // past p: zeros, never stored
                 if (colv) mma(buf);
-                if (more) lstore(buf ^ 1, kb + KB);
+                if (more) lstore(buf ^ 1);
                 __syncthreads();
                 buf ^= 1;
             }
