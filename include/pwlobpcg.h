@@ -341,7 +341,7 @@ pw_status pw_chol_inv(pw_ctx ctx, const void *G, int64_t ldg, int32_t n, void *R
  * dense Rayleigh-Ritz eigenproblem of sec. 3.2 (Algorithm 1) and of the final
  * Rayleigh-Ritz (sec. 3.2, sec. 4.2).  Householder tridiagonalisation,
  * bisection, inverse iteration, re-orthogonalisation, back-transform, FP64;
- * the reduction runs in one workgroup for n <= 192 and over many above.
+ * the reduction runs over many workgroups down to 96 rows, then in one.
  * w: device double[k] ascending; V: device [n x k], ldv >= n.
  * A is overwritten.  1 <= k <= n <= 1024.  Needs the workspace. */
 pw_status pw_small_eigh(pw_ctx ctx, void *A, int64_t lda, int32_t n, int32_t k,

@@ -317,13 +317,13 @@ __global__ void __launch_bounds__(64 * kCholWaves) k_chol_inv(const cd *__restri
 // ---- Hermitian eigensolver ---------------------------------------------------
 // Five stages on the stream:
 //   reduction  A = Q T Q^H, T real tridiagonal (lower Householder):
-//              k_hetrd_la (1 workgroup, n <= 192) or k_trd_col (a launch per column)
+//              k_trd_col (a launch per column) down to 96 rows, k_hetrd_la (1 workgroup)
 //   k_stebz    (k groups)      lowest k eigenvalues of T by 256-point multisection
 //   k_stein_w  (k waves)       eigenvectors of T by inverse iteration, in registers
 //   k_orth_chol2 / k_orth_chol / k_orth (1 workgroup), k_orth_clusters  re-orthogonalisation
 //   k_unmtr_w  (k waves)       back-transform V = Q Z
 //
-// ---- multi-workgroup reduction for n > 192 (the final Rayleigh-Ritz) --------
+// ---- multi-workgroup reduction for n > 96 --------------------------------------
 // H_j = I - tau_j v_j v_j^H, A <- H_j^H A H_j, w = tau y - (|tau|^2 / 2)
 // Re(v^H y) v, A -= w v^H + v w^H, both triangles of the trailing square kept.
 // One launch per column (k_trd_col): a column is a serial chain of two
@@ -348,8 +348,12 @@ __global__ void __launch_bounds__(64 * kCholWaves) k_chol_inv(const cd *__restri
 // eigensolve with few vectors: 1.06 / 1.40 / 2.96 / 8.3 ms with 4, 8 and 32 rows
 // at 256, 512 and 1024 threads; 16 rows at 512 threads 3.1 ms, 32 rows 3.2 ms;
 // 16 rows at 1024 threads 9.2 ms, 8 rows 11.2 ms.
-// (n <= 192 keeps its single-workgroup form: about as fast at n = 192, one launch
-// instead of 192, and one CU instead of the chip while other contexts solve.)
+// The last kTrRest columns are left to k_hetrd_la, whose columns get cheaper with
+// the rows left: 4.0 us at 96 against 4.1 here, 1.4 at 32 (whole eigensolve with 64
+// vectors at n = 192: 1185 us with k_hetrd_la alone, 953 with the last 128
+// columns, 884 with 96; n = 129: 723, 598, 570).  The launch before them (`last`)
+// only applies the update of its predecessor.  96 launches where there was one
+// are no loss for single solves or four at a time (eight at a time: +2 %).
 // Tiles lie on a fixed grid and are numbered in shells of 128 x 128 blocks from
 // the bottom right corner, so that the live ones are a prefix and a tile keeps
 // its workgroup number, hence its XCD and L2, for the whole reduction.
@@ -358,6 +362,7 @@ __global__ void __launch_bounds__(64 * kCholWaves) k_chol_inv(const cd *__restri
 // j - 1 of A receives its reflector in launch j: in launch j - 1 every
 // workgroup still reads that column.
 constexpr int kTrCols = 128;
+constexpr int kTrRest = 96;   // the last columns are left to k_hetrd_la
 constexpr int kTrR256 = 4, kTrR512 = 8, kTrR1024 = 32;
 
 struct TrdState {
@@ -382,7 +387,7 @@ __global__ void k_herm_sym(cd *__restrict__ A, int64_t lda, int n) {
 template <int NT, int TR>
 __global__ void __launch_bounds__(NT)
     k_trd_col(cd *__restrict__ A, int64_t lda, int n, int j, TrdState S, double *__restrict__ dd,
-              double *__restrict__ ee, cd *__restrict__ tau_out) {
+              double *__restrict__ ee, cd *__restrict__ tau_out, bool last) {
     // a wave's load covers TR rows x CS columns, a wave of the tile CS NQ columns
     constexpr int NW = NT / 64, CS = 64 / TR, NQ = kTrCols / (CS * NW), NB = NT / kTrCols;
     __shared__ cd svp[NT], sw[NT], sv[NT];   // v_{j-1}, w_{j-1}, v_j (from row r0)
@@ -399,7 +404,8 @@ __global__ void __launch_bounds__(NT)
     const int rs = q - s * s;
     const int br = nb - 1 - (rs <= s ? s : rs - s - 1), bc = nb - 1 - (rs <= s ? rs : s);
     const int i0 = kTrCols * br + TR * sub, c0 = kTrCols * bc;
-    if (!first && (i0 >= n || i0 + TR - 1 <= j)) return;   // no live row
+    const int lo = last ? j - 1 : j;   // the tiles cover rows and columns > lo
+    if (!first && (i0 >= n || i0 + TR - 1 <= lo)) return;   // no live row
     const int kb = j / kTrCols, r0 = kTrCols * kb, row = r0 + t;   // this thread's row
     // loads: the vectors first, the tile behind them
     const bool in = row >= j && row < n;
@@ -416,14 +422,14 @@ __global__ void __launch_bounds__(NT)
         for (int k = 0; k < NB; ++k)
             if (in && kb + k < nb) yq[k] = yp[(int64_t)(kb + k) * n + row];
     }
-    if (in) c = A[(int64_t)j * lda + row];
+    if (in && !last) c = A[(int64_t)j * lda + row];
     const int i = i0 + lane % TR, cw = c0 + CS * NQ * wave + lane / TR;
-    const bool rok = i > j && i < n;
+    const bool rok = i > lo && i < n;
     cd a[NQ];
 #pragma unroll
     for (int k = 0; k < NQ; ++k) {
         const int col = cw + CS * k;
-        a[k] = rok && col > j && col < n ? A[(int64_t)col * lda + i] : cd{0.0, 0.0};
+        a[k] = rok && col > lo && col < n ? A[(int64_t)col * lda + i] : cd{0.0, 0.0};
     }
     // w_{j-1} and column j
 #pragma unroll
@@ -459,42 +465,43 @@ __global__ void __launch_bounds__(NT)
         c.y -= u1.y + u2.y;
     }
     if (first) {
-        if (row == j) dd[j] = c.x;
+        if (row == j && !last) dd[j] = c.x;
         if (j > 0) {
             if (row > j && in) A[(int64_t)(j - 1) * lda + row] = vi;   // kept for the back-transform
             if (row == j) A[(int64_t)(j - 1) * lda + j] = cd{beta1, 0.0};
         }
     }
-    if (j == n - 1) return;
-    // reflector j
-    const double cc = wave_total(row > j + 1 ? c.x * c.x + c.y * c.y : 0.0);
-    if (lane == 0) red[1][wave] = cc;
-    if (row == j + 1) s_alpha = c;
-    __syncthreads();
-    const double sigma = total(red[1]);
-    const cd alpha = s_alpha;
-    cd tau = {0.0, 0.0}, scale = {0.0, 0.0};
-    double beta = alpha.x;
-    const bool reflect = !(sigma == 0.0 && alpha.y == 0.0);
-    if (reflect) {
-        const double nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + sigma);
-        beta = alpha.x >= 0.0 ? -nrm : nrm;
-        const double dr = alpha.x - beta, di = alpha.y;
-        const double ib = rcp_nr(beta), iden = rcp_nr(dr * dr + di * di);
-        tau = cd{-dr * ib, -di * ib};
-        scale = cd{dr * iden, -di * iden};
-    }
-    cd v = {0.0, 0.0};
-    if (reflect && row == j + 1) v = cd{1.0, 0.0};
-    else if (reflect && row > j + 1 && row < n) v = cmulz(c, scale);
     svp[t] = vi;
     sw[t] = w;
-    sv[t] = v;
-    if (first) {
-        if (in) S.v[j & 1][row] = v;
-        if (t == 0) {
-            tau_out[j] = tau;
-            ee[j] = beta;
+    // reflector j
+    if (!last) {
+        const double cc = wave_total(row > j + 1 ? c.x * c.x + c.y * c.y : 0.0);
+        if (lane == 0) red[1][wave] = cc;
+        if (row == j + 1) s_alpha = c;
+        __syncthreads();
+        const double sigma = total(red[1]);
+        const cd alpha = s_alpha;
+        cd tau = {0.0, 0.0}, scale = {0.0, 0.0};
+        double beta = alpha.x;
+        const bool reflect = !(sigma == 0.0 && alpha.y == 0.0);
+        if (reflect) {
+            const double nrm = sqrt(alpha.x * alpha.x + alpha.y * alpha.y + sigma);
+            beta = alpha.x >= 0.0 ? -nrm : nrm;
+            const double dr = alpha.x - beta, di = alpha.y;
+            const double ib = rcp_nr(beta), iden = rcp_nr(dr * dr + di * di);
+            tau = cd{-dr * ib, -di * ib};
+            scale = cd{dr * iden, -di * iden};
+        }
+        cd v = {0.0, 0.0};
+        if (reflect && row == j + 1) v = cd{1.0, 0.0};
+        else if (reflect && row > j + 1 && row < n) v = cmulz(c, scale);
+        sv[t] = v;
+        if (first) {
+            if (in) S.v[j & 1][row] = v;
+            if (t == 0) {
+                tau_out[j] = tau;
+                ee[j] = beta;
+            }
         }
     }
     __syncthreads();
@@ -504,13 +511,17 @@ __global__ void __launch_bounds__(NT)
 #pragma unroll
     for (int k = 0; k < NQ; ++k) {
         const int col = cw + CS * k;
-        const cd u1 = cmulz(wpi, cconj(svp[col - r0])), u2 = cmulz(vpi, cconj(sw[col - r0])), vc = sv[col - r0];
+        const cd u1 = cmulz(wpi, cconj(svp[col - r0])), u2 = cmulz(vpi, cconj(sw[col - r0]));
         a[k].x -= u1.x + u2.x;
         a[k].y -= u1.y + u2.y;
-        if (rok && col > j && col < n) A[(int64_t)col * lda + i] = a[k];
-        acc.x += a[k].x * vc.x - a[k].y * vc.y;
-        acc.y += a[k].x * vc.y + a[k].y * vc.x;
+        if (rok && col > lo && col < n) A[(int64_t)col * lda + i] = a[k];
+        if (!last) {
+            const cd vc = sv[col - r0];
+            acc.x += a[k].x * vc.x - a[k].y * vc.y;
+            acc.y += a[k].x * vc.y + a[k].y * vc.x;
+        }
     }
+    if (last) return;
     yw[wave][lane] = acc;
     __syncthreads();
     if (wave == 0) {   // the waves' partials in pairs, then the CS lanes of a row
@@ -529,7 +540,7 @@ __global__ void __launch_bounds__(NT)
     }
 }
 
-// ---- register-resident reduction for n <= 32 T (T <= 6) ----------------------
+// ---- register-resident reduction for n <= 32 T (T <= 3; FP32: T <= 6) --------
 // The same Householder sequence as k_trd_col, but the whole
 // matrix stays in registers: 1024 threads on a 32 x 32 grid, each holding one
 // element of every tile b <= a (off-diagonal tiles are stored once and used
@@ -537,6 +548,7 @@ __global__ void __launch_bounds__(NT)
 // whose rows or columns are all finished are skipped.  All sums run in a fixed
 // order (deterministic).  The kernel is k_hetrd_la below.
 constexpr int kRfMaxT = 6;
+constexpr int kRfMaxN = 32 * kRfMaxT;
 
 // Look-ahead form of the register-resident reduction (same Householder
 // sequence and storage of the reflectors): thread (ti, tj) = (t % 32, t / 32)
@@ -1510,7 +1522,7 @@ void launch_chol_inv_f64(const cd *G, int64_t ldg, int n, cd *Rinv, int64_t ldr,
 size_t heev_scratch_bytes(int n, int k) {
     const size_t nch = (size_t)(n + 63) / 64;
     return 8 * 256 + (size_t)n * 16 + 2 * (size_t)n * 8 + (size_t)n * k * 8 +
-           (3 + nch) * (size_t)n * 16;   // n > 192: reflector pair and two sets of ceil(n / 128) partials
+           (3 + nch) * (size_t)n * 16;   // n > 96: reflector pair and two sets of ceil(n / 128) partials
 }
 
 void launch_heev_f64(cd *A, int64_t lda, int n, int k, double *w, cd *V, int64_t ldv, void *scratch,
@@ -1527,24 +1539,8 @@ void launch_heev_f64(cd *A, int64_t lda, int n, int k, double *w, cd *V, int64_t
     double *Z = reinterpret_cast<double *>(p);
     p += align((size_t)n * k * 8);
     // 1. tridiagonalisation (the trailing block of A is overwritten in both triangles)
-    if (n <= 32 * kRfMaxT) {
-        const int T = (n + 31) / 32;
-        auto go = [&](auto r_) {
-            using R = decltype(r_);
-            switch (T) {
-                case 1: hipLaunchKernelGGL((k_hetrd_la<1, R>), dim3(1), dim3(1024), 0, st, A, lda, n, d, e, tau); break;
-                case 2: hipLaunchKernelGGL((k_hetrd_la<2, R>), dim3(1), dim3(1024), 0, st, A, lda, n, d, e, tau); break;
-                case 3: hipLaunchKernelGGL((k_hetrd_la<3, R>), dim3(1), dim3(1024), 0, st, A, lda, n, d, e, tau); break;
-                case 4: hipLaunchKernelGGL((k_hetrd_la<4, R>), dim3(1), dim3(1024), 0, st, A, lda, n, d, e, tau); break;
-                case 5: hipLaunchKernelGGL((k_hetrd_la<5, R>), dim3(1), dim3(1024), 0, st, A, lda, n, d, e, tau); break;
-                default: hipLaunchKernelGGL((k_hetrd_la<6, R>), dim3(1), dim3(1024), 0, st, A, lda, n, d, e, tau); break;
-            }
-        };
-        if (fp32_reduction)
-            go(0.0f);
-        else
-            go(0.0);
-    } else {
+    int j0 = 0;   // columns done before the single-workgroup form takes the rest
+    if (n > (fp32_reduction ? kRfMaxN : kTrRest)) {
         TrdState S;
         S.v[0] = reinterpret_cast<cd *>(p);
         p += align((size_t)n * 16);
@@ -1555,12 +1551,14 @@ void launch_heev_f64(cd *A, int64_t lda, int n, int k, double *w, cd *V, int64_t
         S.yp[1] = S.yp[0] + (size_t)nb * n;
         hipLaunchKernelGGL(k_herm_sym, dim3((unsigned)(((int64_t)n * n + 255) / 256)), dim3(256), 0, st, A, lda,
                            n);
-        for (int j = 0; j < n; ++j) {
-            const int live = std::max(1, nb - (j + 1) / kTrCols);   // blocks of 128 rows or columns
+        j0 = n - kTrRest;
+        for (int j = 0; j <= j0; ++j) {
+            const bool last = j == j0;   // only the update of the column before
+            const int live = nb - (last ? j : j + 1) / kTrCols;   // blocks of 128 rows or columns
             auto col = [&](auto nt, auto tr) {
                 constexpr int NT = decltype(nt)::value, TR = decltype(tr)::value;
                 hipLaunchKernelGGL((k_trd_col<NT, TR>), dim3(live * live * (kTrCols / TR)), dim3(NT), 0, st, A, lda,
-                                   n, j, S, d, e, tau);
+                                   n, j, S, d, e, tau, last);
             };
             const int rows = kTrCols * (nb - j / kTrCols);   // rows of the kernel, one per thread
             if (rows <= 256)
@@ -1571,8 +1569,35 @@ void launch_heev_f64(cd *A, int64_t lda, int n, int k, double *w, cd *V, int64_t
                 col(std::integral_constant<int, 1024>{}, std::integral_constant<int, kTrR1024>{});
         }
     }
+    {
+        cd *const Ar = A + (int64_t)j0 * (lda + 1);
+        const int nr = n - j0;
+        auto go = [&](auto t_, auto r_) {
+            constexpr int T = decltype(t_)::value;
+            hipLaunchKernelGGL((k_hetrd_la<T, decltype(r_)>), dim3(1), dim3(1024), 0, st, Ar, lda, nr, d + j0, e + j0,
+                               tau + j0);
+        };
+        const int T = (nr + 31) / 32;
+        if (fp32_reduction && n <= kRfMaxN) {
+            switch (T) {
+                case 1: go(std::integral_constant<int, 1>{}, 0.0f); break;
+                case 2: go(std::integral_constant<int, 2>{}, 0.0f); break;
+                case 3: go(std::integral_constant<int, 3>{}, 0.0f); break;
+                case 4: go(std::integral_constant<int, 4>{}, 0.0f); break;
+                case 5: go(std::integral_constant<int, 5>{}, 0.0f); break;
+                default: go(std::integral_constant<int, 6>{}, 0.0f); break;
+            }
+        } else {
+            static_assert(kTrRest == 96, "cases below");
+            switch (T) {
+                case 1: go(std::integral_constant<int, 1>{}, 0.0); break;
+                case 2: go(std::integral_constant<int, 2>{}, 0.0); break;
+                default: go(std::integral_constant<int, 3>{}, 0.0); break;
+            }
+        }
+    }
     // 2. eigenvalues, one workgroup each, spread over k CUs
-    const bool lowp = fp32_reduction && n <= 32 * kRfMaxT;
+    const bool lowp = fp32_reduction && n <= kRfMaxN;
     hipLaunchKernelGGL(k_stebz, dim3(k), dim3(kStebzThreads), (size_t)n * 16, st, d, e, n, w,
                        lowp ? (double)FLT_EPSILON : DBL_EPSILON, status);
     // 3. inverse iteration, one wave per eigenvalue

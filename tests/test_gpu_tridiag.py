@@ -48,3 +48,11 @@ def test_reduction(torch_cuda, n, k, kind, pad):
     assert np.abs(wn - ref[:k]).max() <= tol
     assert np.linalg.norm(A @ Vn - Vn * wn, axis=0).max() <= tol
     ctx.close()
+
+
+@pytest.mark.parametrize("n,k,kind,pad", [
+    (96, 96, "dense", 0), (97, 97, "dense", 3), (98, 5, "blocks", 0), (127, 4, "tridiagonal", 0), (129, 129, "dense", 0),
+    (160, 64, "graded", 0), (191, 3, "blocks", 1), (192, 64, "dense", 0), (223, 3, "dense", 0), (225, 3, "tridiagonal", 2)])
+def test_last_columns(torch_cuda, n, k, kind, pad):
+    """The last 96 columns are reduced by one workgroup: the handover, on either side of it."""
+    test_reduction(torch_cuda, n, k, kind, pad)
