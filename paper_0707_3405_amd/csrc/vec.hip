@@ -2,8 +2,8 @@
 // preconditioner, projector table, and small helpers.
 //
 // Per-band reductions are two-level: each workgroup reduces a chunk of rows
-// of one band in a fixed tree order, and a one-workgroup kernel sums the
-// chunk partials in chunk order, so every result is bitwise reproducible.
+// of one band in a fixed tree order, and a small kernel sums the chunk
+// partials in a fixed order, so every result is bitwise reproducible.
 #include <cfloat>
 
 #include "pw_internal.h"
@@ -23,21 +23,33 @@ __device__ __forceinline__ S narrow(double x, double y) {
     return S{(decltype(S::x))x, (decltype(S::y))y};
 }
 
+// Sums of NV values over the workgroup, in every thread: waves by shuffles, then the
+// wave sums in wave order (fixed order, one barrier).
 template <int NV>
 __device__ void wg_reduce(double (&v)[NV], double *red) {
-    const int t = threadIdx.x;
+    constexpr int NW = kThreads / 64;
+    const int wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int q = 0; q < NV; ++q) red[q * kThreads + t] = v[q];
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+        for (int q = 0; q < NV; ++q) v[q] += __shfl_xor(v[q], off);
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int q = 0; q < NV; ++q) red[q * NW + wave] = v[q];
     __syncthreads();
-    for (int s = kThreads / 2; s > 0; s >>= 1) {
-        if (t < s)
 #pragma unroll
-            for (int q = 0; q < NV; ++q) red[q * kThreads + t] += red[q * kThreads + t + s];
-        __syncthreads();
+    for (int q = 0; q < NV; ++q) {
+        v[q] = red[q * NW];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) v[q] += red[q * NW + w];
     }
-#pragma unroll
-    for (int q = 0; q < NV; ++q) v[q] = red[q * kThreads];
 }
+
+// Rows of a chunk handled per thread and pass: their loads go out together (from
+// clamped addresses).  One row at a time left a pass of load latency per row: at
+// npw = 1888 the dots took 5.6 us, 5.2 so, and the residuals 4.1 and 3.5.  (64
+// bands of 34208 rows: 14 and 18 us either way, the time of their bytes.)
+constexpr int kRowsAhead = 4;
 
 // Rayleigh quotient pieces per (chunk, band): Re(x^H Hx), sum T|x|^2 and the
 // norm: |x|^2, or Re(x^H Ox) in the generalized form (OX given).
@@ -46,23 +58,31 @@ __global__ void __launch_bounds__(kThreads)
     k_band_dots(const S *__restrict__ X, int64_t ldx, const S *__restrict__ HX, int64_t ldhx,
                 const double *__restrict__ kin, int64_t npw, int nb, double *__restrict__ part,
                 const S *__restrict__ OX, int64_t ldox) {
-    __shared__ double red[3 * kThreads];
+    __shared__ double red[3 * kThreads / 64];
     const int c = blockIdx.x, b = blockIdx.y;
     const int64_t r0 = (int64_t)c * kChunk, r1 = min(npw, r0 + kChunk);
     const S *x = X + (int64_t)b * ldx;
     const S *h = HX + (int64_t)b * ldhx;
     const S *o = OX ? OX + (int64_t)b * ldox : nullptr;
     double v[3] = {0.0, 0.0, 0.0};
-    for (int64_t r = r0 + threadIdx.x; r < r1; r += kThreads) {
-        const cd a = widen(x[r]), hb = widen(h[r]);
-        const double n2 = a.x * a.x + a.y * a.y;
-        v[0] += a.x * hb.x + a.y * hb.y;
-        v[1] += kin[r] * n2;
-        if (o) {
-            const cd ob = widen(o[r]);
+    for (int64_t rb = r0 + threadIdx.x; rb < r1; rb += kRowsAhead * kThreads) {
+        S xs[kRowsAhead], hs[kRowsAhead], os[kRowsAhead];
+        double ks[kRowsAhead];
+#pragma unroll
+        for (int u = 0; u < kRowsAhead; ++u) {
+            const int64_t r = rb + u * kThreads < r1 ? rb + u * kThreads : rb;
+            xs[u] = x[r];
+            hs[u] = h[r];
+            ks[u] = kin[r];
+            os[u] = o ? o[r] : xs[u];
+        }
+#pragma unroll
+        for (int u = 0; u < kRowsAhead; ++u) {
+            if (rb + u * kThreads >= r1) break;
+            const cd a = widen(xs[u]), hb = widen(hs[u]), ob = widen(os[u]);
+            v[0] += a.x * hb.x + a.y * hb.y;
+            v[1] += ks[u] * (a.x * a.x + a.y * a.y);
             v[2] += a.x * ob.x + a.y * ob.y;
-        } else {
-            v[2] += n2;
         }
     }
     wg_reduce<3>(v, red);
@@ -74,17 +94,45 @@ __global__ void __launch_bounds__(kThreads)
     }
 }
 
+// The final sums of the chunk partials: a group of 64 bands per workgroup, a thread
+// each, where there are few chunks; else a wave per band, its lanes over the chunks
+// (64 bands of 17 chunks: 5.8 us by threads, 4.4 by waves for the dots, 6.2 and
+// 4.5 for the norms; 16 bands of one chunk: 1.5 and 2.4, 1.6 and 2.6).
+constexpr int kFewChunks = 4;
+int final_groups(int nchunk, int nb) { return nchunk <= kFewChunks ? (nb + 63) / 64 : nb; }
+// this thread's band and first chunk, and the chunk stride
+struct FinalPart {
+    int b, c, step;
+};
+__device__ __forceinline__ FinalPart final_part(int nchunk) {
+    const int t = threadIdx.x, g = blockIdx.x;
+    return nchunk <= kFewChunks ? FinalPart{64 * g + t, 0, 1} : FinalPart{g, t, 64};
+}
+__device__ __forceinline__ double final_sum(double x, int step) {
+    if (step > 1) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
+    }
+    return x;
+}
+
 // out[0..nb): theta, out[nb..2nb): E_kin, out[2nb..3nb): |x|^2
-__global__ void k_band_dots_final(const double *__restrict__ part, int nchunk, int nb,
+__global__ void __launch_bounds__(64) k_band_dots_final(const double *__restrict__ part, int nchunk, int nb,
                                   double *__restrict__ theta, double *__restrict__ ekin_nrm) {
-    for (int b = threadIdx.x; b < nb; b += blockDim.x) {
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-        for (int c = 0; c < nchunk; ++c) {
+    const FinalPart f = final_part(nchunk);
+    const int b = f.b;
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+    if (b < nb)
+        for (int c = f.c; c < nchunk; c += f.step) {
             const double *p = part + ((int64_t)c * nb + b) * 3;
             s0 += p[0];
             s1 += p[1];
             s2 += p[2];
         }
+    s0 = final_sum(s0, f.step);
+    s1 = final_sum(s1, f.step);
+    s2 = final_sum(s2, f.step);
+    if (b < nb && (f.step == 1 || threadIdx.x == 0)) {
         const double inv = s2 > 0 ? 1.0 / s2 : 0.0;
         theta[b] = s0 * inv;
         ekin_nrm[b] = s1 * inv;
@@ -99,7 +147,7 @@ __global__ void __launch_bounds__(kThreads)
             const double *__restrict__ kin, int64_t npw, int nb, const double *__restrict__ theta,
             const double *__restrict__ ekin, S *__restrict__ W, int64_t ldw,
             double *__restrict__ part) {
-    __shared__ double red[kThreads];
+    __shared__ double red[kThreads / 64];
     const int c = blockIdx.x, b = blockIdx.y;
     const int64_t r0 = (int64_t)c * kChunk, r1 = min(npw, r0 + kChunk);
     const S *x = X + (int64_t)b * ldx;
@@ -108,15 +156,29 @@ __global__ void __launch_bounds__(kThreads)
     const double ek = fmax(ekin[b], 1e-3);
     const double iek = 1.0 / ek;
     double v[1] = {0.0};
-    for (int64_t r = r0 + threadIdx.x; r < r1; r += kThreads) {
-        const cd a = widen(x[r]), hb = widen(h[r]);
-        const cd rr = {hb.x - th * a.x, hb.y - th * a.y};
-        v[0] += rr.x * rr.x + rr.y * rr.y;
-        if (W) {
-            const double xx = kin[r] * iek;
-            const double num = 27.0 + xx * (18.0 + xx * (12.0 + xx * 8.0));
-            const double k = num / (num + 16.0 * xx * xx * xx * xx);
-            W[(int64_t)b * ldw + r] = narrow<S>(k * rr.x, k * rr.y);
+    for (int64_t rb = r0 + threadIdx.x; rb < r1; rb += kRowsAhead * kThreads) {
+        S xs[kRowsAhead], hs[kRowsAhead];
+        double ks[kRowsAhead];
+#pragma unroll
+        for (int u = 0; u < kRowsAhead; ++u) {
+            const int64_t r = rb + u * kThreads < r1 ? rb + u * kThreads : rb;
+            xs[u] = x[r];
+            hs[u] = h[r];
+            ks[u] = kin[r];
+        }
+#pragma unroll
+        for (int u = 0; u < kRowsAhead; ++u) {
+            const int64_t r = rb + u * kThreads;
+            if (r >= r1) break;
+            const cd a = widen(xs[u]), hb = widen(hs[u]);
+            const cd rr = {hb.x - th * a.x, hb.y - th * a.y};
+            v[0] += rr.x * rr.x + rr.y * rr.y;
+            if (W) {
+                const double xx = ks[u] * iek;
+                const double num = 27.0 + xx * (18.0 + xx * (12.0 + xx * 8.0));
+                const double k = num / (num + 16.0 * xx * xx * xx * xx);
+                W[(int64_t)b * ldw + r] = narrow<S>(k * rr.x, k * rr.y);
+            }
         }
     }
     wg_reduce<1>(v, red);
@@ -144,16 +206,18 @@ __global__ void __launch_bounds__(kThreads)
 
 // status (optional): the context's status word, appended as res[nb] so that one
 // copy brings the norms and the breakdown flags to the host
-__global__ void k_resid_final(const double *__restrict__ part, int nchunk, int nb,
+__global__ void __launch_bounds__(64) k_resid_final(const double *__restrict__ part, int nchunk, int nb,
                               const double *__restrict__ nrm2, double *__restrict__ res,
                               const int *__restrict__ status) {
-    if (status && threadIdx.x == 0) res[nb] = (double)*status;
-    for (int b = threadIdx.x; b < nb; b += blockDim.x) {
-        double s = 0.0;
-        for (int c = 0; c < nchunk; ++c) s += part[(int64_t)c * nb + b];
-        const double n2 = nrm2 ? nrm2[b] : 1.0;
-        res[b] = sqrt(s / (n2 > 0 ? n2 : 1.0));
-    }
+    if (status && blockIdx.x == 0 && threadIdx.x == 0) res[nb] = (double)*status;
+    const FinalPart f = final_part(nchunk);
+    const int b = f.b;
+    const double n2 = nrm2 && b < nb ? nrm2[b] : 1.0;
+    double s = 0.0;
+    if (b < nb)
+        for (int c = f.c; c < nchunk; c += f.step) s += part[(int64_t)c * nb + b];
+    s = final_sum(s, f.step);
+    if (b < nb && (f.step == 1 || threadIdx.x == 0)) res[b] = sqrt(s / (n2 > 0 ? n2 : 1.0));
 }
 
 // beta_{a,lm}(q) = pref exp(-|q|^2/2) Y_lm(q^) exp(-i q.R_a)
@@ -265,7 +329,7 @@ void band_dots_impl(const S *X, int64_t ldx, const S *HX, int64_t ldhx, const do
     const int nchunk = (int)((npw + kChunk - 1) / kChunk);
     hipLaunchKernelGGL(k_band_dots<S>, dim3(nchunk, nb), dim3(kThreads), 0, st, X, ldx, HX, ldhx, kin,
                        npw, nb, part, OX, ldox);
-    hipLaunchKernelGGL(k_band_dots_final, dim3(1), dim3(256), 0, st, part, nchunk, nb, theta, ekin);
+    hipLaunchKernelGGL(k_band_dots_final, dim3(final_groups(nchunk, nb)), dim3(64), 0, st, part, nchunk, nb, theta, ekin);
     PW_HIP(hipGetLastError());
 }
 void launch_band_dots(const cd *X, int64_t ldx, const cd *HX, int64_t ldhx, const double *kin,
@@ -287,7 +351,7 @@ void resid_impl(const S *X, int64_t ldx, const S *HX, int64_t ldhx, const double
     hipLaunchKernelGGL(k_resid<S>, dim3(nchunk, nb), dim3(kThreads), 0, st, X, ldx, HX, ldhx, kin, npw,
                        nb, theta, ekin, W, ldw, part);
     // ekin array carries |x|^2 in its second half (see k_band_dots_final)
-    hipLaunchKernelGGL(k_resid_final, dim3(1), dim3(256), 0, st, part, nchunk, nb, ekin + nb, res, status);
+    hipLaunchKernelGGL(k_resid_final, dim3(final_groups(nchunk, nb)), dim3(64), 0, st, part, nchunk, nb, ekin + nb, res, status);
     PW_HIP(hipGetLastError());
 }
 void launch_resid_precond(const cd *X, int64_t ldx, const cd *HX, int64_t ldhx, const double *kin,
