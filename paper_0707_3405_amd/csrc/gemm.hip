@@ -303,7 +303,7 @@ __global__ void __launch_bounds__(kThreads)
         for (int64_t kb = kbeg; kb < kend; kb += KB) {
             if constexpr (kZeroAtLoad<T>) {
                 const bool more = kb + KB < kend;
-                gload(kb + KB);   // past the chunk end: clamped, never stored
+                if (more) gload(kb + KB);
                 mma(buf);
                 if (more) lstore(buf ^ 1, kb + KB);
             } else {
@@ -544,7 +544,8 @@ __global__ void __launch_bounds__(kThreads)
 // loads while the others multiply, instead of all of them waiting in step.
 // K = 34208: complex64 432 x 64 82 -> 73 us, 192 x 64 41 -> 37, FP64 432 x 64
 // 129 -> 126, 64 x 64 26.4 -> 27.1; 82592: complex64 748 x 64 303 -> 272, FP64
-// 494 -> 484; K = 11392: complex64 256 x 23 26.4 -> 23.2.  (k_gemm_tn_lds
+// 494 -> 484; K = 11392: complex64 256 x 23 26.4 -> 23.2.  (Nothing is loaded past the
+// last block: 0.4 us of a call with few blocks.)  (k_gemm_tn_lds
 // measured 3-6 % slower with such loads, and 3-14 % with the priorities.)
 constexpr int kNnMaxRb = 5;
 template <class T>
@@ -655,7 +656,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(s
             int buf = 0;
             for (int kb = 0; kb < p; kb += KB) {
                 const bool more = kb + KB < p;
-                gload(kb + KB);   // past p: zeros, never stored
+                if (more) gload(kb + KB);
                 if (colv) mma(buf);
                 if (more) lstore(buf ^ 1);
                 __syncthreads();
