@@ -458,8 +458,8 @@ struct PlaneLane {
 // drift apart: one wave's LDS accesses run under another's arithmetic.  Per plane
 // at N = 96 ~13.6k VALU wave instructions and about as many LDS cycles, mostly
 // writes (8 bytes a lane at best 85 B per cycle; reads run at 256).  Against the
-// form with a barrier after each of ~14 stages, 64 bands: N = 96 413 -> 300 us
-// FP64, 192 -> 165 FP32; N = 72, 92 bands, 290 -> 172 FP64.
+// form with a barrier after each of ~14 stages, 64 bands: N = 96 413 -> 307 us
+// FP64, 198 -> 176 FP32; N = 72, 92 bands, 290 -> 172 FP64.
 template <class P, class T, bool HALF>
 __global__ void __launch_bounds__(64 * kPlaneWaves) k_plane(const ApplyItems<T> items, const T *__restrict__ vperm,
                                                             int nb) {
