@@ -9,6 +9,7 @@
 //    inverse iteration, classical Gram-Schmidt applied twice, back-transform.
 #include <algorithm>
 #include <cfloat>
+#include <cmath>
 #include <type_traits>
 
 #include "pw_internal.h"
@@ -789,13 +790,16 @@ struct TriBounds {
 
 // Gershgorin interval, pivot floor and norm of the tridiagonal matrix, by the
 // whole workgroup (min and max: exact in any order).  red: 3 doubles per wave.
+// fmin and fmax drop a NaN, so an entry that is not finite makes the norm
+// infinite (the interval is meaningless then).
 __device__ TriBounds tri_bounds(const double *__restrict__ dd, const double *__restrict__ ee, int n, double *red) {
     double gl = DBL_MAX, gu = -DBL_MAX, tnorm = 0.0;
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         const double r = (i > 0 ? fabs(ee[i - 1]) : 0.0) + (i + 1 < n ? fabs(ee[i]) : 0.0);
         gl = fmin(gl, dd[i] - r);
         gu = fmax(gu, dd[i] + r);
-        tnorm = fmax(tnorm, fabs(dd[i]) + r);
+        const double a = fabs(dd[i]) + r;
+        tnorm = fmax(tnorm, a <= DBL_MAX ? a : HUGE_VAL);
     }
     for (int off = 32; off > 0; off >>= 1) {
         gl = fmin(gl, __shfl_xor(gl, off));
@@ -896,14 +900,21 @@ __global__ void __launch_bounds__(kStebzThreads) k_stebz(const double *__restric
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     constexpr int NP = kStebzThreads;   // interior points per round
     const TriBounds tb = tri_bounds(dd, ee, n, red);
-    // exact scaling to norm <= 1 (none for a zero or non-finite norm)
-    const int ex = (tb.tnorm > 0.0 && tb.tnorm <= DBL_MAX) ? __builtin_amdgcn_frexp_exp(tb.tnorm) : 0;
+    const int idx = blockIdx.x;
+    if (!(tb.tnorm <= DBL_MAX)) {   // NaN or infinity in the matrix, or norms past the range
+        if (t == 0) {
+            w[idx] = NAN;
+            atomicOr(status, 4);
+        }
+        return;
+    }
+    // exact scaling to norm <= 1 (none for a zero norm)
+    const int ex = tb.tnorm > 0.0 ? __builtin_amdgcn_frexp_exp(tb.tnorm) : 0;
     for (int i = t; i < n; i += kStebzThreads) {
         const double e = i > 0 ? __builtin_amdgcn_ldexp(ee[i - 1], -ex) : 0.0;
         de[i] = double2{__builtin_amdgcn_ldexp(dd[i], -ex), e * e};
     }
     __syncthreads();
-    const int idx = blockIdx.x;
     double lo = tb.gl, hi = tb.gu;
     for (int round = 0; round < 18; ++round) {
         const double width = hi - lo;
