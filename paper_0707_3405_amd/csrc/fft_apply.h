@@ -587,32 +587,44 @@ void run_apply_split(const ApplyItems<T> &items, int nk, const T *vperm, int nb,
     const int spb = tune.fft_spb > 0 ? tune.fft_spb : kSticksPerBlock;
     const size_t e = sizeof(cpx<T>);
     const size_t sm13 = (size_t)N * e + (size_t)spb * (N + 1) * e;
-    int nst_max = 0, ncx_max = 0;
-    bool half = P::R1 == 8;
-    for (int k = 0; k < nk; ++k) {
-        nst_max = std::max(nst_max, items.it[k].sp.nst);
-        ncx_max = std::max(ncx_max, items.it[k].sp.ncx);
-        half = half && items.it[k].sp.quarter;
-    }
+    int nst_max = 0;
+    for (int k = 0; k < nk; ++k) nst_max = std::max(nst_max, items.it[k].sp.nst);
     dim3 g13((nst_max + spb - 1) / spb, nb, nk);
     // rows in flight asked for by the tuning: a cap on the waves
-    const int nw = plane_waves<P, T>(ncx_max, tune.fft_rb > 0 ? std::max(1, std::min(kPlaneWaves, tune.fft_rb / W::RG)) : 0);
-    PW_REQUIRE(nw >= 1, PW_ERR_ARG, "FFT plane does not fit in LDS");
-    const size_t sm2 = plane_columns<P, T>(ncx_max) + nw * W::xbytes();
-    auto plane = [&](auto h) {
+    const int most = tune.fft_rb > 0 ? std::max(1, std::min(kPlaneWaves, tune.fft_rb / W::RG)) : 0;
+    // The plane pass of the items with spheres inside the middle half (h) or not: a
+    // launch for each kind that there is.  The pruned form and the full one round
+    // differently, so an item's form may not depend on the others of its batch.
+    auto plane = [&](auto h, bool launch) {
         constexpr bool H = decltype(h)::value;
-        ensure_smem_limit((const void *)k_plane<P, T, H>, sm2);
-        hipLaunchKernelGGL((k_plane<P, T, H>), dim3(N * nb, 1, nk), dim3(64 * nw), sm2, st, items, vperm, nb);
+        int n = 0, ncx_max = 0, of[kMaxApplyBatch];
+        for (int k = 0; k < nk; ++k)
+            if (H == (P::R1 == 8 && items.it[k].sp.quarter)) {
+                of[n++] = k;
+                ncx_max = std::max(ncx_max, items.it[k].sp.ncx);
+            }
+        if (!n) return;
+        const int nw = plane_waves<P, T>(ncx_max, most);
+        PW_REQUIRE(nw >= 1, PW_ERR_ARG, "FFT plane does not fit in LDS");
+        const size_t sm2 = plane_columns<P, T>(ncx_max) + nw * W::xbytes();
+        if (!launch) return ensure_smem_limit((const void *)k_plane<P, T, H>, sm2);
+        auto go = [&](const ApplyItems<T> &kind) {
+            hipLaunchKernelGGL((k_plane<P, T, H>), dim3(N * nb, 1, n), dim3(64 * nw), sm2, st, kind, vperm, nb);
+        };
+        if (n == nk) return go(items);
+        ApplyItems<T> kind;
+        for (int k = 0; k < n; ++k) kind.it[k] = items.it[of[k]];
+        go(kind);
     };
+    auto planes = [&](bool launch) {
+        if constexpr (P::R1 == 8) plane(std::true_type{}, launch);
+        plane(std::false_type{}, launch);
+    };
+    planes(false);   // refuse before anything is launched
     ensure_smem_limit((const void *)k_zinv<P, T>, sm13);
     ensure_smem_limit((const void *)k_zfwd<P, T>, sm13);
     hipLaunchKernelGGL((k_zinv<P, T>), g13, dim3(kThreads), sm13, st, items, spb);
-    if constexpr (P::R1 == 8) {
-        if (half) plane(std::true_type{});
-        else plane(std::false_type{});
-    } else {
-        plane(std::false_type{});
-    }
+    planes(true);
     hipLaunchKernelGGL((k_zfwd<P, T>), g13, dim3(kThreads), sm13, st, items, spb);
     PW_HIP(hipGetLastError());
 }
