@@ -289,7 +289,10 @@ pw_status pw_lobpcg_solve_batch(pw_ctx *ctxs, int32_t n, int32_t nbands, int32_t
  * [j0][j1][j2] (the layout of pw_set_local_potential).  Needs basis and a
  * workspace of at least block * N * (sticks rounded up to 16) * 16 + N^3 * 8 +
  * nb * 8 bytes (any workspace sized by pw_workspace_size for the same block
- * is enough for nb <= nbands).  Deterministic; synchronises the stream. */
+ * is enough for nb <= nbands).  The bands are summed in up to 64 groups, by the
+ * basis and nb; a workspace with room for a grid per group takes the groups
+ * side by side, a smaller one in turn, with the same bits.  Deterministic;
+ * synchronises the stream. */
 pw_status pw_density(pw_ctx ctx, const void *X, int64_t ldx, int32_t nb, const double *occ,
                      void *rho);
 /* Residual norms ||H x_j - theta_j x_j||_2 of the last solve, host double[nbands]. */

@@ -8,16 +8,17 @@ namespace {
 
 // ---- density: per z-plane inverse xy transforms, occ |psi|^2 accumulated -----
 // part[group][z][y][x position] = sum of occ[b] |psi_b(x, y, z)|^2 over the bands
-// of the group (psi without the 1/sqrt(Omega) factor; b = blockIdx.y, + groups,
-// ...), added to what `part` holds.  One workgroup owns one plane of one group
-// and adds its bands in order, so no two threads write one element and the sum
-// is deterministic.  REG: a wave per row group, its sums in registers over the
+// of the group (psi without the 1/sqrt(Omega) factor; band b of the launch is in
+// group (first + b) % groups and has occupation occ[b * ostride]), added to what
+// `part` holds.  One workgroup owns one plane of one group and adds its bands in
+// order, so no two threads write one element and the sum is deterministic.  REG: a wave per row group, its sums in registers over the
 // bands; else any count of waves, the sums in memory.  256 bands at N = 96: 4652
 // us in one group with the bands in series and a barrier per stage, 790 us so;
 // 842 with four waves and the sums in L2 (three groups of sums per wave spill).
 template <class P, class T, bool HALF, bool REG>
 __global__ void __launch_bounds__(64 * kPlaneWaves)
-    k_plane_rho(const ApplyItems<T> items, int nb, const double *__restrict__ occ, double *__restrict__ part) {
+    k_plane_rho(const ApplyItems<T> items, int nb, const double *__restrict__ occ, int ostride, double *__restrict__ part,
+                int groups, int first) {
     const SphereDev &sp = items.it[0].sp;
     const cpx<T> *__restrict__ S = items.it[0].S;
     using W = PlaneWave<P>;
@@ -26,7 +27,7 @@ __global__ void __launch_bounds__(64 * kPlaneWaves)
     cpx<T> *A = reinterpret_cast<cpx<T> *>(smem_raw);
     const int z = blockIdx.x, ncx = sp.ncx, nw = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     auto *xb = reinterpret_cast<typename Slot<T>::type *>(smem_raw + plane_columns<P, T>(ncx)) + wave * (W::RPI * W::ldx());
-    double *rz = part + ((int64_t)blockIdx.y * N + z) * N * N;
+    double *rz = part + ((int64_t)((first + blockIdx.y) % groups) * N + z) * N * N;
     PlaneLane<P, T, HALF> L;
     L.init(sp.twid);
     const int cg = (ncx + nw - 1) / nw;
@@ -39,8 +40,8 @@ __global__ void __launch_bounds__(64 * kPlaneWaves)
 #pragma unroll
         for (int k = 0; k < R2; ++k) acc[k] = (L.act2 && row(wave) < N) ? rz[row(wave) * N + L.k1 * R2 + k] : 0.0;
     }
-    for (int band = blockIdx.y; band < nb; band += gridDim.y) {
-        const double f = occ[band];
+    for (int band = blockIdx.y; band < nb; band += groups) {
+        const double f = occ[(int64_t)band * ostride];
         L.columns_in(sp, S + ((int64_t)band * N + z) * sp.ldst, A, c0, c1);
         __syncthreads();
         for (int g = wave; g < W::NG; g += nw) {
@@ -65,14 +66,16 @@ __global__ void __launch_bounds__(64 * kPlaneWaves)
     }
 }
 
-// rho[x][y][z] = scale * sum of the groups' part[group][z][y][position of x]
+// rho[x][y][z] = scale * sum of the groups' part[group][z][y][position of x], on top
+// of what rho holds if `add`
 template <class P>
-__global__ void k_rho_permute(const double *__restrict__ part, int groups, double scale, double *__restrict__ rho) {
+__global__ void k_rho_permute(const double *__restrict__ part, int groups, double scale, double *__restrict__ rho,
+                              bool add) {
     constexpr int N = P::N;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (int64_t)N * N * N) return;
     const int z = (int)(i % N), y = (int)((i / N) % N), x = (int)(i / ((int64_t)N * N));
-    double s = 0.0;
+    double s = add ? rho[i] : 0.0;
     for (int g = 0; g < groups; ++g) s += part[(((int64_t)g * N + z) * N + y) * N + digit_rev<P>(x)];
     rho[i] = s * scale;
 }
@@ -213,8 +216,8 @@ struct DensityShape {
 };
 
 template <int N>
-void run_density(const SphereDev &sp, const cd *X, int64_t ldx, int nb, const double *occ, double *part, int groups,
-                 cd *S, hipStream_t st) {
+void run_density(const SphereDev &sp, const cd *X, int64_t ldx, int nb, const double *occ, int ostride, double *part,
+                 int groups, int first, cd *S, hipStream_t st) {
     using P = Split<N>;
     using D = DensityShape<N>;
     const int spb = kSticksPerBlock;
@@ -231,7 +234,7 @@ void run_density(const SphereDev &sp, const cd *X, int64_t ldx, int nb, const do
         constexpr bool H = decltype(h)::value, R = decltype(r)::value;
         ensure_smem_limit((const void *)k_plane_rho<P, double, H, R>, sm2);
         hipLaunchKernelGGL((k_plane_rho<P, double, H, R>), dim3(N, std::min(groups, nb)), dim3(64 * nw), sm2, st, items,
-                           nb, occ, part);
+                           nb, occ, ostride, part, groups, first);
     };
     auto by_sum = [&](auto h) {
         if (D::reg(sp.ncx)) rho(h, std::true_type{});
@@ -260,13 +263,13 @@ int density_resident(const SphereDev &sp) {
     }
 }
 
-void launch_density_accumulate(const SphereDev &sp, const cd *X, int64_t ldx, int nb, const double *occ, double *part,
-                               int groups, cd *S, hipStream_t st) {
+void launch_density_accumulate(const SphereDev &sp, const cd *X, int64_t ldx, int nb, const double *occ, int ostride,
+                               double *part, int groups, int first, cd *S, hipStream_t st) {
     if (nb <= 0) return;
     switch (sp.n) {
 #define PW_CASE(NN)                                                         \
-    case NN:                                                                \
-        run_density<NN>(sp, X, ldx, nb, occ, part, groups, S, st);          \
+    case NN:                                                                        \
+        run_density<NN>(sp, X, ldx, nb, occ, ostride, part, groups, first, S, st);  \
         return;
         PW_FFT_SIZES(PW_CASE)
 #undef PW_CASE
@@ -275,13 +278,13 @@ void launch_density_accumulate(const SphereDev &sp, const cd *X, int64_t ldx, in
     }
 }
 
-void launch_density_finish(const double *part, int n, int groups, double scale, double *rho, hipStream_t st) {
+void launch_density_finish(const double *part, int n, int groups, double scale, double *rho, bool add, hipStream_t st) {
     const int64_t tot = (int64_t)n * n * n;
     const dim3 grid((unsigned)((tot + 255) / 256));
     switch (n) {
 #define PW_CASE(NN)                                                                                         \
-    case NN:                                                                                                \
-        hipLaunchKernelGGL((k_rho_permute<Split<NN>>), grid, dim3(256), 0, st, part, groups, scale, rho);   \
+    case NN:                                                                                                    \
+        hipLaunchKernelGGL((k_rho_permute<Split<NN>>), grid, dim3(256), 0, st, part, groups, scale, rho, add);  \
         break;
         PW_FFT_SIZES(PW_CASE)
 #undef PW_CASE

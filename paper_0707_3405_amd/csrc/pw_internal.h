@@ -77,12 +77,13 @@ void launch_fft_apply(const SphereDev &sp, const double *v_zyx, const cd *X, int
 // complex64 form: v_zyx as float
 void launch_fft_apply(const SphereDev &sp, const float *v_zyx, const cf *X, int64_t ldx,
                       cf *Y, int64_t ldy, int nb, cf *S, hipStream_t st);
-// Density: part[g][z][y][x position] += sum of occ[b] |psi_b|^2 over the columns
-// b = g, g + groups, ... of X (psi = inverse transform of the sphere
-// coefficients, no 1/sqrt(Omega)); then rho[x][y][z] = scale * the groups' sum.
-void launch_density_accumulate(const SphereDev &sp, const cd *X, int64_t ldx, int nb, const double *occ, double *part,
-                               int groups, cd *S, hipStream_t st);
-void launch_density_finish(const double *part, int n, int groups, double scale, double *rho, hipStream_t st);
+// Density: part[g][z][y][x position] += sum of occ[b * ostride] |psi_b|^2 over the
+// columns b of X with (first + b) % groups = g (psi = inverse transform of the sphere
+// coefficients, no 1/sqrt(Omega)); then rho[x][y][z] = scale * (rho if `add`, + the
+// groups in order).
+void launch_density_accumulate(const SphereDev &sp, const cd *X, int64_t ldx, int nb, const double *occ, int ostride,
+                               double *part, int groups, int first, cd *S, hipStream_t st);
+void launch_density_finish(const double *part, int n, int groups, double scale, double *rho, bool add, hipStream_t st);
 int density_resident(const SphereDev &sp);   // plane workgroups of the density resident per CU
 bool fft_size_supported(int n);
 std::vector<int> fft_supported_sizes();

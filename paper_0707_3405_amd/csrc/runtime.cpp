@@ -293,15 +293,18 @@ size_t density_bytes(const pw_ctx_s &c, int chunk, int nb) {
 }
 
 // Band groups of the density's plane pass (n workgroups each, `resident` of them
-// per CU): the bands of a chunk are dealt over the groups, and each group costs
-// a read and a write of its own sum of the grid.  One group left 160 of the 256
-// CUs idle at n = 96.  Rounds of workgroups times bands per group, at about
-// n^2 ns a plane, against 16 n^3 bytes a group at ~5 TB/s.
-int density_groups(int n, int resident, int nc, int most) {
-    const int slots = 256 * std::max(1, resident);
+// per CU): the bands are dealt over the groups, and each group costs a read and a
+// write of its own sum of the grid.  One group left 160 of the 256 CUs idle at
+// n = 96.  Rounds of workgroups times bands per group, at about n^2 ns a plane,
+// against 16 n^3 bytes a group at ~5 TB/s, for the bands of a full block of 64 (or
+// all, if fewer): neither the workspace nor its block size enters, as the groups
+// fix the order of the sum.
+constexpr int kDensityBands = 64;
+int density_groups(int n, int resident, int nb) {
+    const int slots = 256 * std::max(1, resident), nc = std::min(nb, kDensityBands);
     int best = 1;
     double cost = HUGE_VAL;
-    for (int g = 1; g <= std::min(nc, most); ++g) {
+    for (int g = 1; g <= nc; ++g) {
         const double c = (double)((n * g + slots - 1) / slots) * std::max(1, resident) * ((nc + g - 1) / g) + 3.2e-3 * n * g;
         if (c < cost) {
             cost = c;
@@ -1604,21 +1607,27 @@ pw_status pw_density(pw_ctx c, const void *X, int64_t ldx, int32_t nb, const dou
         a.base = c->ws;
         cd *S = a.take<cd>((size_t)chunk * c->n * c->sp.ldst);
         double *docc = a.take<double>((size_t)nb);
-        const int64_t room = (int64_t)(c->ws_bytes - align_up(a.used, 256)) / (n3 * 8);   // >= 1 by the check above
-        const int groups = density_groups(c->n, pw::density_resident(c->sp), std::min(chunk, nb), (int)std::min<int64_t>(room, 64));
-        double *part = a.take<double>((size_t)n3 * groups);
-        hipStream_t st = c->stream;
-        pw::launch_zero(reinterpret_cast<cd *>(part), n3 / 2 * groups, n3 / 2 * groups, 1, st);   // N is even
-        PW_HIP(hipMemcpyAsync(docc, occ, sizeof(double) * nb, hipMemcpyHostToDevice, st));
-        const cd *Xc = static_cast<const cd *>(X);
-        for (int b0 = 0; b0 < nb; b0 += chunk) {
-            const int nc = std::min(chunk, nb - b0);
-            pw::launch_density_accumulate(c->sp, Xc + (int64_t)b0 * ldx, ldx, nc, docc + b0, part, groups, S, st);
-        }
         const double *m = c->cell;
         const double omega = std::fabs(m[0] * (m[4] * m[8] - m[5] * m[7]) - m[1] * (m[3] * m[8] - m[5] * m[6]) +
                                        m[2] * (m[3] * m[7] - m[4] * m[6]));
-        pw::launch_density_finish(part, c->n, groups, 1.0 / omega, static_cast<double *>(rho), st);
+        // every group's sum at once where the workspace holds them, else one group after
+        // the other through one grid: the same additions in the same order
+        const int groups = density_groups(c->n, pw::density_resident(c->sp), nb);
+        const size_t room = (c->ws_bytes - align_up(a.used, 256)) / (n3 * 8);   // >= 1 by the check above
+        const int at_once = room >= (size_t)groups ? groups : 1, rounds = groups / at_once;
+        double *part = a.take<double>((size_t)n3 * at_once);
+        hipStream_t st = c->stream;
+        PW_HIP(hipMemcpyAsync(docc, occ, sizeof(double) * nb, hipMemcpyHostToDevice, st));
+        const cd *Xc = static_cast<const cd *>(X);
+        for (int g = 0; g < rounds; ++g) {   // bands g, g + rounds, ...
+            const int ng = (nb - g + rounds - 1) / rounds;
+            pw::launch_zero(reinterpret_cast<cd *>(part), n3 / 2 * at_once, n3 / 2 * at_once, 1, st);   // N is even
+            for (int b0 = 0; b0 < ng; b0 += chunk)
+                pw::launch_density_accumulate(c->sp, Xc + ((int64_t)b0 * rounds + g) * ldx, ldx * rounds, std::min(chunk, ng - b0),
+                                              docc + (int64_t)b0 * rounds + g, rounds, part, at_once, b0 % at_once, S, st);
+            pw::launch_density_finish(part, c->n, at_once, g + 1 == rounds ? 1.0 / omega : 1.0, static_cast<double *>(rho),
+                                      g > 0, st);
+        }
         PW_HIP(hipStreamSynchronize(st));   // occ is read from host memory above
         return PW_OK;
     });
