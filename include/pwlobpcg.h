@@ -326,9 +326,9 @@ pw_status pw_block_update(pw_ctx ctx, const void *A, int64_t lda, const void *C,
                           int64_t K, int32_t p, int32_t q, double alpha, double beta,
                           void *Y, int64_t ldy);
 /* The same two products on complex64 blocks (the PW_PREC_MIXED iteration):
- * A, B, Y complex64; C complex128 (pw_gram_mixed: FP32 products and sums
- * within each K chunk, chunk partials summed in FP64; pw_block_update_mixed:
- * C rounded to complex64 as it is read, FP32 products and sums). */
+ * A, B, Y complex64; C complex128 (pw_gram_mixed: FP32 products, FP32 sums of
+ * at most 192 rows and of those within each K chunk, chunk partials summed in
+ * FP64; pw_block_update_mixed: C rounded to complex64 as it is read, FP32 products and sums). */
 pw_status pw_gram_mixed(pw_ctx ctx, const void *A, int64_t lda, const void *B, int64_t ldb,
                         int64_t K, int32_t p, int32_t q, void *C, int64_t ldc);
 pw_status pw_block_update_mixed(pw_ctx ctx, const void *A, int64_t lda, const void *C,

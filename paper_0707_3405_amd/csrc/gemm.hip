@@ -26,8 +26,9 @@
 //
 // The same kernels serve complex128 blocks (v_mfma_f64_16x16x4f64) and the
 // complex64 blocks of the mixed-precision form (v_mfma_f32_16x16x4f32, FP32
-// products and accumulation within a K chunk; the chunk partials are summed
-// in double).  Small coefficient matrices are always complex128 and are
+// products and accumulation within a K chunk, there in sums of at most 192
+// rows that are added up at the end of each; the chunk partials are summed in
+// double).  Small coefficient matrices are always complex128 and are
 // rounded to the block type as they are loaded.
 //
 // A third form serves the projector products of the BF16 mixed iteration:
@@ -65,6 +66,7 @@ struct Mfma<float> {
 
 constexpr int kTile = 64;      // workgroup tile (complex elements) per dimension
 constexpr int kThreads = 256;  // 4 waves in a 2 x 2 arrangement, 32 x 32 each
+constexpr int kRun = 12;       // k-blocks in one FP32 sum of the complex64 TN product, at most
 
 
 // Loading operand tiles.  complex64: the loads carry no condition, their
@@ -171,7 +173,7 @@ __device__ __forceinline__ void mma_bf16(const cpx<float> (&a)[2][4], const cpx<
 // split-bf16 products (complex64 only): one 16x16x16 MFMA per product covers a
 // whole k-block, lane group g holding k = 4g .. 4g + 3 in both operands.
 template <class T, bool BF>
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 1 : 3)))
     k_gemm_tn_lds(const cpx<T> *__restrict__ A, int64_t lda, const cpx<T> *__restrict__ B,
                   int64_t ldb, int64_t K, int p, int q, int tiles_m, int tiles_n,
                   int nsplit, cpx<T> *__restrict__ part, int herm) {
@@ -245,6 +247,21 @@ __global__ void __launch_bounds__(kThreads)
     for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b) t1[a][b] = t2[a][b] = t3[a][b] = v4{0, 0, 0, 0};
+    // complex64: the sums above are added to sr + i si and start again every kRun
+    // k-blocks, so that no FP32 sum of products is longer than 192 rows, however
+    // long the chunk: the error grows with the root of that length.  rms error of
+    // the Gram of random blocks over their norms, chunks of up to 256 rows (twice
+    // the partials) / long chunks without runs / so: 432 x 64 at K = 34181 2.2e-9 /
+    // 3.0e-9 / 1.8e-9, 512 x 512 6.3e-9 / 7.3e-9 / 2.0e-9, 748 x 64 at K = 82561
+    // 2.8e-9 / 3.2e-9 / 1.2e-9.  Time of the last two 480 -> 490 and 246 -> 252 us.
+    constexpr bool kRuns = sizeof(T) == 4;
+    v4 sr[2][2], si[2][2];
+    if constexpr (kRuns) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) sr[a][b] = si[a][b] = v4{0, 0, 0, 0};
+    }
     const int ia = (wave & 1) * 32, jb = (wave >> 1) * 32;
     // sub-tiles wholly outside p x q are skipped (uniform per wave)
     bool live[2][2];
@@ -253,6 +270,17 @@ __global__ void __launch_bounds__(kThreads)
 #pragma unroll
         for (int nj = 0; nj < 2; ++nj)
             live[mi][nj] = tm * kTile + ia + 16 * mi < p && tn * kTile + jb + 16 * nj < q;
+    auto end_run = [&] {
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                if (!live[a][b]) continue;
+                sr[a][b] += t1[a][b] + t2[a][b];
+                si[a][b] += t3[a][b] - t1[a][b] + t2[a][b];
+                t1[a][b] = t2[a][b] = t3[a][b] = v4{0, 0, 0, 0};
+            }
+    };
     // FULL: every sub-tile of the wave lies inside p x q (all but edge tiles),
     // so the MFMAs run without the per-sub-tile branches
     auto mma_t = [&](int buf, auto full) {
@@ -299,8 +327,14 @@ __global__ void __launch_bounds__(kThreads)
         // 3-4 % slower so.
         if constexpr (!kZeroAtLoad<T>) gload(kbeg + KB);
         __syncthreads();
-        int buf = 0;
+        int buf = 0, left = kRun;
         for (int64_t kb = kbeg; kb < kend; kb += KB) {
+            if constexpr (kRuns) {
+                if (left-- == 0) {
+                    end_run();
+                    left = kRun - 1;
+                }
+            }
             if constexpr (kZeroAtLoad<T>) {
                 const bool more = kb + KB < kend;
                 if (more) gload(kb + KB);
@@ -317,6 +351,7 @@ __global__ void __launch_bounds__(kThreads)
             buf ^= 1;
         }
     }
+    if constexpr (kRuns) end_run();
     cpx<T> *P = part + (size_t)split * (herm ? (size_t)ntile * kTile * kTile : (size_t)p * q);
     const int i0 = tm * kTile + ia, j0 = tn * kTile + jb;
 #pragma unroll
@@ -329,8 +364,10 @@ __global__ void __launch_bounds__(kThreads)
                 const int j = j0 + 16 * nj + li;
                 const size_t at = herm ? ((size_t)tile * kTile + (j - tn * kTile)) * kTile + (i - tm * kTile)
                                        : (size_t)j * p + i;
-                if (i < p && j < q)
-                    P[at] = cpx<T>{t1[mi][nj][r] + t2[mi][nj][r], t3[mi][nj][r] - t1[mi][nj][r] + t2[mi][nj][r]};
+                if (i < p && j < q) {
+                    if constexpr (kRuns) P[at] = cpx<T>{sr[mi][nj][r], si[mi][nj][r]};
+                    else P[at] = cpx<T>{t1[mi][nj][r] + t2[mi][nj][r], t3[mi][nj][r] - t1[mi][nj][r] + t2[mi][nj][r]};
+                }
             }
 }
 
@@ -725,7 +762,8 @@ int device_cu_count() {
 // products stop at chunks of 5 k-blocks (8 for one tile, whose partials are
 // summed by few workgroups), then of 3 while that leaves CUs idle, then at 64
 // workgroups (256 x 23 at K = 11392: 44 splits 39.7 us, 128 30.6; 96 x 96 at
-// K = 3425: 14 splits 33 us, 64 21).
+// K = 3425: 14 splits 33 us, 64 21).  complex64 products of up to 16 runs of kRun
+// blocks have 16 chunks at least: their FP32 sums are as short as the chunks.
 // target > 0: a cap on the workgroups from the tuning.
 int choose_split(int64_t K, int tiles, int target, bool cplx64) {
     const int64_t nkb = (K + 15) / 16;
@@ -733,14 +771,15 @@ int choose_split(int64_t K, int tiles, int target, bool cplx64) {
     const int64_t longc = nkb / (tiles == 1 ? 8 : 5);
     const int64_t mid = std::min<int64_t>(256 / tiles, nkb / 3);
     const int64_t shortc = std::min<int64_t>(64 / tiles, nkb);
-    return (int)std::max<int64_t>(1, std::min(slots / tiles, std::max({longc, mid, shortc})));
+    const int64_t least = cplx64 && nkb <= 16 * kRun ? std::min<int64_t>((target > 0 ? target : 1024) / tiles, std::min<int64_t>(nkb, 16)) : 1;
+    return (int)std::max({(int64_t)1, least, std::min(slots / tiles, std::max({longc, mid, shortc}))});
 }
 
 }  // namespace
 
 size_t gemm_tn_part_elems(int64_t K, int p, int q, int *nsplit_out) {
     const int tiles = ((p + kTile - 1) / kTile) * ((q + kTile - 1) / kTile);
-    const int ns = choose_split(K, tiles, kTnSplitMax, false);   // the most any target gives
+    const int ns = choose_split(K, tiles, kTnSplitMax, true);   // the most that any target and type gives
     if (nsplit_out) *nsplit_out = ns;
     return (size_t)ns * p * q;
 }
