@@ -180,7 +180,7 @@ pw_status pw_apply_H(pw_ctx ctx, const void *X, int64_t ldx, void *Y, int64_t ld
  * them together).  The contexts share one device, one stream and one FFT
  * grid; their spheres, kinetic energies, projectors and stick buffers are
  * their own, and the local potential of ctxs[0] serves them all, as do its
- * launch parameters (pw_set_tuning: radix split, FFT tiling, split-K target).
+ * launch parameters (pw_set_tuning: radix split, FFT tiling, split-K cap).
  * Each of the three FFT passes is one launch over every (k-point, band) work
  * item (the plane pass two where some spheres lie inside the middle half of
  * the grid and some reach beyond it); the projector products of each context
@@ -200,13 +200,13 @@ pw_status pw_apply_H_batch(pw_ctx const *ctxs, int32_t nk, const void *const *X,
  * pw_autotune, the timings behind the choice (ms per launch).  The sticks and
  * rows change the partition of the work only (the FFT results are bitwise the
  * same); the radix split changes the order of the FFT's operations and the
- * split-K target that of the Gram sums, so both may change the rounding. */
+ * split-K cap that of the Gram sums, so both may change the rounding. */
 typedef struct {
     int32_t fft_sticks_per_block;   /* z passes: sticks per workgroup, 0 or 1..64 (default 16) */
     int32_t fft_plane_rows;         /* plane pass: rows a workgroup works on at once (a cap on its waves),
                                        0 or 1..128 (default: what LDS and registers hold) */
-    int32_t gemm_split_workgroups;  /* cap on the workgroups of a split-K TN product, 0 or 1..1024 (default
-                                       512 or, for long complex64 products, 768) */
+    int32_t gemm_split_workgroups;  /* cap on the workgroups of a split-K TN product, 0 or 1..1024, below
+                                       the built-in limits by its size (one to three per compute unit) */
     double apply_ms_default, apply_ms_tuned;   /* local H X of nb bands */
     double gemm_ms_default, gemm_ms_tuned;     /* 3m x 3m Gram over npw (+ projector overlaps) */
     int32_t fft_radix2;   /* radix split of the length-N FFTs: N = (N / R2) R2, both factors
@@ -219,7 +219,7 @@ typedef struct {
  * differ in npw, grid and projector count): times the local H X of nb bands
  * (1 <= nb <= block of the workspace) for every radix split of the grid's FFT
  * length x sticks per block {16, 32, 64} x plane rows {16, 32, 48, 96}, and the Rayleigh-Ritz Gram (3 block x 3 block over
- * npw) plus the projector overlaps for split targets {384, 512, 768, 1024},
+ * npw) plus the projector overlaps with and without a split cap of 384,
  * with HIP events on the context stream (mean of 5 after a warm-up); keeps
  * the fastest of each (or the default when nothing beats it) for later
  * calls on this context and reports it in *out.  Needs basis, potential,

@@ -764,14 +764,15 @@ int device_cu_count() {
 // workgroups (256 x 23 at K = 11392: 44 splits 39.7 us, 128 30.6; 96 x 96 at
 // K = 3425: 14 splits 33 us, 64 21).  complex64 products of up to 16 runs of kRun
 // blocks have 16 chunks at least: their FP32 sums are as short as the chunks.
-// target > 0: a cap on the workgroups from the tuning.
+// target > 0: a cap on the workgroups from the tuning, below these.
 int choose_split(int64_t K, int tiles, int target, bool cplx64) {
     const int64_t nkb = (K + 15) / 16;
-    const int64_t slots = target > 0 ? target : tiles <= (cplx64 ? 2 : 1) ? 256 : (cplx64 && nkb * tiles >= 20 * 768) ? 768 : 512;
+    const int64_t built_in = tiles <= (cplx64 ? 2 : 1) ? 256 : (cplx64 && nkb * tiles >= 20 * 768) ? 768 : 512;
+    const int64_t cap = target > 0 ? target : 1024, slots = std::min(built_in, cap);
     const int64_t longc = nkb / (tiles == 1 ? 8 : 5);
     const int64_t mid = std::min<int64_t>(256 / tiles, nkb / 3);
     const int64_t shortc = std::min<int64_t>(64 / tiles, nkb);
-    const int64_t least = cplx64 && nkb <= 16 * kRun ? std::min<int64_t>((target > 0 ? target : 1024) / tiles, std::min<int64_t>(nkb, 16)) : 1;
+    const int64_t least = cplx64 && nkb <= 16 * kRun ? std::min<int64_t>(cap / tiles, std::min<int64_t>(nkb, 16)) : 1;
     return (int)std::max({(int64_t)1, least, std::min(slots / tiles, std::max({longc, mid, shortc}))});
 }
 
@@ -779,7 +780,7 @@ int choose_split(int64_t K, int tiles, int target, bool cplx64) {
 
 size_t gemm_tn_part_elems(int64_t K, int p, int q, int *nsplit_out) {
     const int tiles = ((p + kTile - 1) / kTile) * ((q + kTile - 1) / kTile);
-    const int ns = choose_split(K, tiles, kTnSplitMax, true);   // the most that any target and type gives
+    const int ns = std::max(choose_split(K, tiles, 0, false), choose_split(K, tiles, 0, true));
     if (nsplit_out) *nsplit_out = ns;
     return (size_t)ns * p * q;
 }

@@ -112,7 +112,7 @@ void launch_fft_apply_batch(const FftApplyItem<float> *items, int nk, const floa
 struct Tuning {
     int fft_spb = 0;        // sticks per workgroup of the z passes
     int fft_rb = 0;         // rows a plane workgroup works on at once (a cap on its waves)
-    int tn_split_wgs = 0;   // target workgroup count of a split-K TN launch
+    int tn_split_wgs = 0;   // cap on the workgroups of a split-K TN launch
     int fft_r2 = 0;         // second factor R2 of the radix split N = R1 R2 (0: default)
 };
 // radix splits N = R1 R2 available for length n (R2 values) and the default R2
@@ -120,7 +120,7 @@ std::vector<int> fft_radix_splits(int n);
 int fft_default_r2(int n);
 const Tuning &thread_tuning();
 const Tuning *set_thread_tuning(const Tuning *t);   // returns the previous record
-constexpr int kTnSplitMax = 1024;   // largest split target; partial buffers are sized for it
+constexpr int kTnSplitMax = 1024;   // largest split cap
 
 // Complex GEMMs on MFMA over complex128 (cd) or complex64 (cf) blocks;
 // small outputs and coefficient matrices are always complex128.
