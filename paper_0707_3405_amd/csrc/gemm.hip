@@ -43,6 +43,22 @@
 #include "pw_internal.h"
 
 namespace pw {
+
+// compute units of the current device (queried once per process and device)
+int device_cu_count() {
+    static std::atomic<int> cached[64];
+    int dev = 0;
+    PW_HIP(hipGetDevice(&dev));
+    if (dev < 0 || dev >= 64) dev = 0;
+    int n = cached[dev].load(std::memory_order_relaxed);
+    if (!n) {
+        PW_HIP(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev));
+        if (n <= 0) n = 256;
+        cached[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
 namespace {
 
 template <class T>
@@ -738,21 +754,6 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(s
     }
 }
 
-// compute units of the current device (queried once per process and device)
-int device_cu_count() {
-    static std::atomic<int> cached[64];
-    int dev = 0;
-    PW_HIP(hipGetDevice(&dev));
-    if (dev < 0 || dev >= 64) dev = 0;
-    int n = cached[dev].load(std::memory_order_relaxed);
-    if (!n) {
-        PW_HIP(hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev));
-        if (n <= 0) n = 256;
-        cached[dev].store(n, std::memory_order_relaxed);
-    }
-    return n;
-}
-
 // Splits of K.  Every workgroup of the launch is resident at once (two per CU;
 // complex64 products of 20 k-blocks a workgroup or more take three) and all have
 // the same number of k-blocks to within one (one tile, or two in complex64: one per CU, as the sum of
@@ -765,12 +766,12 @@ int device_cu_count() {
 // K = 3425: 14 splits 33 us, 64 21).  complex64 products of up to 16 runs of kRun
 // blocks have 16 chunks at least: their FP32 sums are as short as the chunks.
 // target > 0: a cap on the workgroups from the tuning, below these.
-int choose_split(int64_t K, int tiles, int target, bool cplx64) {
+int choose_split(int64_t K, int tiles, int target, bool cplx64, int cu) {
     const int64_t nkb = (K + 15) / 16;
-    const int64_t built_in = tiles <= (cplx64 ? 2 : 1) ? 256 : (cplx64 && nkb * tiles >= 20 * 768) ? 768 : 512;
+    const int64_t built_in = tiles <= (cplx64 ? 2 : 1) ? cu : (cplx64 && nkb * tiles >= 20 * 3 * cu) ? 3 * cu : 2 * cu;
     const int64_t cap = target > 0 ? target : 1024, slots = std::min(built_in, cap);
     const int64_t longc = nkb / (tiles == 1 ? 8 : 5);
-    const int64_t mid = std::min<int64_t>(256 / tiles, nkb / 3);
+    const int64_t mid = std::min<int64_t>(cu / tiles, nkb / 3);
     const int64_t shortc = std::min<int64_t>(64 / tiles, nkb);
     const int64_t least = cplx64 && nkb <= 16 * kRun ? std::min<int64_t>(cap / tiles, std::min<int64_t>(nkb, 16)) : 1;
     return (int)std::max({(int64_t)1, least, std::min(slots / tiles, std::max({longc, mid, shortc}))});
@@ -779,10 +780,18 @@ int choose_split(int64_t K, int tiles, int target, bool cplx64) {
 }  // namespace
 
 size_t gemm_tn_part_elems(int64_t K, int p, int q, int *nsplit_out) {
-    const int tiles = ((p + kTile - 1) / kTile) * ((q + kTile - 1) / kTile);
-    const int ns = std::max(choose_split(K, tiles, 0, false), choose_split(K, tiles, 0, true));
+    const int tiles_m = (p + kTile - 1) / kTile, tiles_n = (q + kTile - 1) / kTile;
+    // for an MI355X: a host-only context has no device to ask, and more splits than fit
+    // the partial buffer are never taken
+    auto most = [&](int tiles) { return std::max(choose_split(K, tiles, 0, false, 256), choose_split(K, tiles, 0, true, 256)); };
+    const int ns = most(tiles_m * tiles_n);
     if (nsplit_out) *nsplit_out = ns;
-    return (size_t)ns * p * q;
+    size_t elems = (size_t)ns * p * q;
+    if (p == q) {   // the Hermitian form: whole tiles, on and above the diagonal
+        const int nt = tiles_m * (tiles_m + 1) / 2;
+        elems = std::max(elems, (size_t)most(nt) * nt * kTile * kTile);
+    }
+    return elems;
 }
 
 // herm: A^H B is Hermitian (B = H A for a Hermitian H, p = q); only the
@@ -797,7 +806,7 @@ void gemm_tn_impl(const cpx<T> *A, int64_t lda, const cpx<T> *B, int64_t ldb, in
     herm = herm && p == q && tiles_m >= 2 && !scale_row && beta == 0.0;
     const int ntile = herm ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
     const size_t per_split = herm ? (size_t)ntile * kTile * kTile : (size_t)p * q;
-    int ns = choose_split(K, ntile, thread_tuning().tn_split_wgs, sizeof(T) == 4);
+    int ns = choose_split(K, ntile, thread_tuning().tn_split_wgs, sizeof(T) == 4, device_cu_count());
     if ((size_t)ns * per_split > part_elems) ns = (int)(part_elems / per_split);
     PW_REQUIRE(ns >= 1, PW_ERR_NOMEM, "GEMM partial buffer too small");
     const int total = ntile * ns;

@@ -120,6 +120,7 @@ std::vector<int> fft_radix_splits(int n);
 int fft_default_r2(int n);
 const Tuning &thread_tuning();
 const Tuning *set_thread_tuning(const Tuning *t);   // returns the previous record
+int device_cu_count();   // compute units of the current device
 constexpr int kTnSplitMax = 1024;   // largest split cap
 
 // Complex GEMMs on MFMA over complex128 (cd) or complex64 (cf) blocks;

@@ -301,7 +301,7 @@ size_t density_bytes(const pw_ctx_s &c, int chunk, int nb) {
 // fix the order of the sum.
 constexpr int kDensityBands = 64;
 int density_groups(int n, int resident, int nb) {
-    const int slots = 256 * std::max(1, resident), nc = std::min(nb, kDensityBands);
+    const int slots = pw::device_cu_count() * std::max(1, resident), nc = std::min(nb, kDensityBands);
     int best = 1;
     double cost = HUGE_VAL;
     for (int g = 1; g <= nc; ++g) {
