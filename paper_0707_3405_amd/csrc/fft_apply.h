@@ -568,15 +568,15 @@ constexpr int kSticksPerBlock = 16;   // default sticks per workgroup of the z p
 // that are no multiple of 4 load the SIMDs unevenly).  With fewer workgroups,
 // up to 12 in one (N = 120, FP32: 2 x 4 458, 1 x 12 402), but for R2 = 16, whose
 // items collide in the banks whatever the waves (N = 128, FP32: 533 and 558).
-// most > 0: a cap from the tuning.  0 if even one wave does not fit.
+// most > 0: a cap from the tuning, below these.  0 if even one wave does not fit.
 template <class P, class T>
 int plane_waves(int ncx, int most) {
     using W = PlaneWave<P>;
     auto lds = [&](int nw) { return plane_columns<P, T>(ncx) + nw * W::xbytes(); };
-    int nw = std::min(most > 0 ? most : kPlaneWaves, W::NG);
-    if (most <= 0 && lds(4) * ((sizeof(T) == 8 || P::R2 == 16) ? 2 : 3) <= kLdsMax) nw = std::min(nw, 4);
+    int nw = std::min(kPlaneWaves, W::NG);
+    if (lds(4) * ((sizeof(T) == 8 || P::R2 == 16) ? 2 : 3) <= kLdsMax) nw = std::min(nw, 4);
     while (nw > 0 && lds(nw) > kLdsMax) --nw;
-    return nw;
+    return most > 0 ? std::min(nw, most) : nw;
 }
 
 template <class P, class T>
