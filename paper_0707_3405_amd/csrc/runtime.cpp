@@ -1617,11 +1617,11 @@ pw_status pw_density(pw_ctx c, const void *X, int64_t ldx, int32_t nb, const dou
         const int at_once = room >= (size_t)groups ? groups : 1, rounds = groups / at_once;
         double *part = a.take<double>((size_t)n3 * at_once);
         hipStream_t st = c->stream;
-        PW_HIP(hipMemcpyAsync(docc, occ, sizeof(double) * nb, hipMemcpyHostToDevice, st));
         const cd *Xc = static_cast<const cd *>(X);
         for (int g = 0; g < rounds; ++g) {   // bands g, g + rounds, ...
             const int ng = (nb - g + rounds - 1) / rounds;
             pw::launch_zero(reinterpret_cast<cd *>(part), n3 / 2 * at_once, n3 / 2 * at_once, 1, st);   // N is even
+            if (g == 0) PW_HIP(hipMemcpyAsync(docc, occ, sizeof(double) * nb, hipMemcpyHostToDevice, st));
             for (int b0 = 0; b0 < ng; b0 += chunk)
                 pw::launch_density_accumulate(c->sp, Xc + ((int64_t)b0 * rounds + g) * ldx, ldx * rounds, std::min(chunk, ng - b0),
                                               docc + (int64_t)b0 * rounds + g, rounds, part, at_once, b0 % at_once, S, st);
