@@ -561,20 +561,31 @@ __global__ void __launch_bounds__(kThreads) k_zfwd(const ApplyItems<T> items, in
 constexpr int kSticksPerBlock = 16;   // default sticks per workgroup of the z passes
 
 // Waves of a plane workgroup.  Four, one per SIMD, where LDS (kept columns and
-// an exchange buffer per wave) holds two such workgroups in FP64, three in FP32:
-// workgroups out of step with each other fill the LDS phases of one with the
-// arithmetic of another, which waves behind one barrier do not (N = 96, FP64,
-// 64 bands: 2 x 4 waves 333 us, 1 x 12 379; N = 72: 3 x 4 140, 1 x 9 218; counts
-// that are no multiple of 4 load the SIMDs unevenly).  With fewer workgroups,
-// up to 12 in one (N = 120, FP32: 2 x 4 458, 1 x 12 402), but for R2 = 16, whose
-// items collide in the banks whatever the waves (N = 128, FP32: 533 and 558).
+// an exchange buffer per wave) holds enough such workgroups, two in FP64, in FP32
+// four (three above N = 96): workgroups out of step with each other fill the LDS
+// phases of one with the arithmetic of another, which waves behind one barrier do
+// not (N = 96, FP64, 64 bands: 2 x 4 waves 333 us, 1 x 12 379; N = 72: 3 x 4 140,
+// 1 x 9 218; counts that are no multiple of 4 load the SIMDs unevenly).  FP32
+// where they don't fit: eight or six waves, two workgroups (64 bands, 2 x 8 and
+// otherwise: N = 72, 45 columns 148 and, 3 x 4, 159 us; 63 columns 220 and, 1 x 12,
+// 272; N = 96, 61 columns 287 and 377; 2 x 6: N = 108, 53 columns 405 and 447).
+// With one workgroup up to 12 waves (N = 120, FP32: 2 x 4 458, 1 x 12 402), but
+// for R2 = 16, whose items collide in the banks whatever the waves (N = 128, FP32:
+// 533 and 558).  With no more planes than compute units nothing else runs beside
+// a workgroup, and up to 12 waves shorten it (one band, 12 / 4 waves: N = 72 FP64
+// 23.2 / 27.0 us, N = 80 26.4 / 30.6, N = 96 FP32 23.5 / 30.0).
 // most > 0: a cap from the tuning, below these.  0 if even one wave does not fit.
 template <class P, class T>
-int plane_waves(int ncx, int most) {
+int plane_waves(int ncx, int most, int64_t planes) {
     using W = PlaneWave<P>;
+    constexpr bool F32 = sizeof(T) == 4 && P::R2 != 16;
     auto lds = [&](int nw) { return plane_columns<P, T>(ncx) + nw * W::xbytes(); };
-    int nw = std::min(kPlaneWaves, W::NG);
-    if (lds(4) * ((sizeof(T) == 8 || P::R2 == 16) ? 2 : 3) <= kLdsMax) nw = std::min(nw, 4);
+    int nw = kPlaneWaves;
+    if (planes > device_cu_count()) {
+        if (lds(4) * (!F32 ? 2 : P::N <= 96 ? 4 : 3) <= kLdsMax) nw = 4;
+        else if (F32 && lds(6) * 2 <= kLdsMax) nw = lds(8) * 2 <= kLdsMax ? 8 : 6;
+    }
+    nw = std::min(nw, W::NG);
     while (nw > 0 && lds(nw) > kLdsMax) --nw;
     return most > 0 ? std::min(nw, most) : nw;
 }
@@ -604,7 +615,7 @@ void run_apply_split(const ApplyItems<T> &items, int nk, const T *vperm, int nb,
                 ncx_max = std::max(ncx_max, items.it[k].sp.ncx);
             }
         if (!n) return;
-        const int nw = plane_waves<P, T>(ncx_max, most);
+        const int nw = plane_waves<P, T>(ncx_max, most, (int64_t)N * nb * n);
         PW_REQUIRE(nw >= 1, PW_ERR_ARG, "FFT plane does not fit in LDS");
         const size_t sm2 = plane_columns<P, T>(ncx_max) + nw * W::xbytes();
         if (!launch) return ensure_smem_limit((const void *)k_plane<P, T, H>, sm2);
