@@ -192,7 +192,7 @@ template <class T, bool BF>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 1 : 3)))
     k_gemm_tn_lds(const cpx<T> *__restrict__ A, int64_t lda, const cpx<T> *__restrict__ B,
                   int64_t ldb, int64_t K, int p, int q, int tiles_m, int tiles_n,
-                  int nsplit, cpx<T> *__restrict__ part, int herm) {
+                  int nsplit, int64_t kq, int kr, cpx<T> *__restrict__ part, int herm) {
     using M = Mfma<T>;
     using v4 = typename M::v4;
     constexpr int KB = 16, LDC = KB + 1;
@@ -217,10 +217,10 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(s
     }
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int li = lane & 15, g = lane >> 4;
-    // k-blocks [nkb split / nsplit, nkb (split + 1) / nsplit): chunks differ by at most one
-    const int64_t nkb = (K + KB - 1) / KB;
-    const int64_t kbeg = nkb * split / nsplit * KB;
-    const int64_t kend = min(K, nkb * (split + 1) / nsplit * KB);
+    // chunks of kq k-blocks, the first kr of kq + 1.  (From the launch: 64-bit divisions
+    // here cost each call 0.4 us.)
+    const int64_t kbeg = (split * kq + min(split, kr)) * KB;
+    const int64_t kend = min(K, kbeg + (kq + (split < kr)) * KB);
 
     // global -> LDS assignment: instruction u covers columns 16 wave + 4u + g, rows li
     const cpx<T> *Ag[4];
@@ -812,8 +812,9 @@ void gemm_tn_impl(const cpx<T> *A, int64_t lda, const cpx<T> *B, int64_t ldb, in
     const int total = ntile * ns;
     // partials in the block type (the buffer is sized for complex128)
     cpx<T> *pt = reinterpret_cast<cpx<T> *>(part);
+    const int64_t nkb = (K + 15) / 16;
     hipLaunchKernelGGL((k_gemm_tn_lds<T, BF>), dim3(total), dim3(kThreads), 0, st, A, lda, B, ldb, K, p, q,
-                       tiles_m, tiles_n, ns, pt, herm ? 1 : 0);
+                       tiles_m, tiles_n, ns, nkb / ns, (int)(nkb % ns), pt, herm ? 1 : 0);
     const int64_t n = (int64_t)per_split;
     const unsigned rgroups = (unsigned)((n + 63) / 64);
     if (rgroups < 256)
