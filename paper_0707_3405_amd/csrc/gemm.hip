@@ -188,11 +188,11 @@ __device__ __forceinline__ void mma_bf16(const cpx<float> (&a)[2][4], const cpx<
 // block's MFMAs (two LDS buffers, one barrier per block).  BF selects the
 // split-bf16 products (complex64 only): one 16x16x16 MFMA per product covers a
 // whole k-block, lane group g holding k = 4g .. 4g + 3 in both operands.
-template <class T, bool BF>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 1 : 3)))
+template <class T, bool BF, bool RUNS>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(RUNS ? 3 : 1)))
     k_gemm_tn_lds(const cpx<T> *__restrict__ A, int64_t lda, const cpx<T> *__restrict__ B,
                   int64_t ldb, int64_t K, int p, int q, int tiles_m, int tiles_n,
-                  int nsplit, int64_t kq, int kr, cpx<T> *__restrict__ part, int herm) {
+                  int nsplit, int64_t kq, int kr, int run, cpx<T> *__restrict__ part, int herm) {
     using M = Mfma<T>;
     using v4 = typename M::v4;
     constexpr int KB = 16, LDC = KB + 1;
@@ -263,16 +263,16 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(s
     for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b) t1[a][b] = t2[a][b] = t3[a][b] = v4{0, 0, 0, 0};
-    // complex64: the sums above are added to sr + i si and start again every kRun
-    // k-blocks, so that no FP32 sum of products is longer than 192 rows, however
-    // long the chunk: the error grows with the root of that length.  rms error of
-    // the Gram of random blocks over their norms, chunks of up to 256 rows (twice
-    // the partials) / long chunks without runs / so: 432 x 64 at K = 34181 2.2e-9 /
-    // 3.0e-9 / 1.8e-9, 512 x 512 6.3e-9 / 7.3e-9 / 2.0e-9, 748 x 64 at K = 82561
-    // 2.8e-9 / 3.2e-9 / 1.2e-9.  Time of the last two 480 -> 490 and 246 -> 252 us.
-    constexpr bool kRuns = sizeof(T) == 4;
+    // RUNS (complex64, chunks of more than one run): the sums above are added to
+    // sr + i si and start again every `run` k-blocks, so that no FP32 sum of products
+    // is longer than 192 rows, however long the chunk: the error grows with the root
+    // of that length.  rms error of the Gram of random blocks over their norms, chunks
+    // of up to 256 rows (twice the partials) / long chunks without runs / so: 432 x 64
+    // at K = 34181 2.2e-9 / 3.0e-9 / 1.8e-9, 512 x 512 6.3e-9 / 7.3e-9 / 2.0e-9,
+    // 748 x 64 at K = 82561 2.8e-9 / 3.2e-9 / 1.2e-9.  Time of the last two 474 ->
+    // 485 and 237 -> 241 us; chunks of one run keep the plain form.
     v4 sr[2][2], si[2][2];
-    if constexpr (kRuns) {
+    if constexpr (RUNS) {
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -340,34 +340,40 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(s
         // complex64: loads run two blocks ahead of their use and the stores come
         // before the MFMAs, which go first among the waves of a SIMD: 512 x 512
         // at K = 34208 493 -> 466 us.  FP64, whose MFMAs take twice as long, was
-        // 3-4 % slower so.
-        if constexpr (!kZeroAtLoad<T>) gload(kbeg + KB);
+        // 3-4 % slower so.  Past the chunk end nothing is loaded or stored, but in
+        // long chunks (RUNS), where the conditions cost 1 %: addresses are clamped
+        // there, and the zeros that are stored are not used.
+        if (!kZeroAtLoad<T> && (RUNS || kbeg + KB < kend)) gload(kbeg + KB);
         __syncthreads();
-        int buf = 0, left = kRun;
-        for (int64_t kb = kbeg; kb < kend; kb += KB) {
-            if constexpr (kRuns) {
-                if (left-- == 0) {
-                    end_run();
-                    left = kRun - 1;
-                }
-            }
-            if constexpr (kZeroAtLoad<T>) {
+        int buf = 0;
+        int64_t kb = kbeg;
+        auto blocks_to = [&](int64_t end) {
+            for (; kb < end; kb += KB) {
                 const bool more = kb + KB < kend;
-                if (more) gload(kb + KB);
-                mma(buf);
-                if (more) lstore(buf ^ 1, kb + KB);
-            } else {
-                lstore(buf ^ 1, kb + KB);
-                gload(kb + 2 * KB);   // past the chunk end: clamped, stored as zeros and not used
-                __builtin_amdgcn_s_setprio(1);
-                mma(buf);
-                __builtin_amdgcn_s_setprio(0);
+                if constexpr (kZeroAtLoad<T>) {
+                    if (more) gload(kb + KB);
+                    mma(buf);
+                    if (more) lstore(buf ^ 1, kb + KB);
+                } else {
+                    if (RUNS || more) lstore(buf ^ 1, kb + KB);
+                    if (RUNS || kb + 2 * KB < kend) gload(kb + 2 * KB);
+                    __builtin_amdgcn_s_setprio(1);
+                    mma(buf);
+                    __builtin_amdgcn_s_setprio(0);
+                }
+                __syncthreads();
+                buf ^= 1;
             }
-            __syncthreads();
-            buf ^= 1;
+        };
+        if constexpr (RUNS) {
+            while (kb < kend) {
+                blocks_to(min(kend, kb + (int64_t)run * KB));
+                end_run();
+            }
+        } else {
+            blocks_to(kend);
         }
     }
-    if constexpr (kRuns) end_run();
     cpx<T> *P = part + (size_t)split * (herm ? (size_t)ntile * kTile * kTile : (size_t)p * q);
     const int i0 = tm * kTile + ia, j0 = tn * kTile + jb;
 #pragma unroll
@@ -381,7 +387,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(s
                 const size_t at = herm ? ((size_t)tile * kTile + (j - tn * kTile)) * kTile + (i - tm * kTile)
                                        : (size_t)j * p + i;
                 if (i < p && j < q) {
-                    if constexpr (kRuns) P[at] = cpx<T>{sr[mi][nj][r], si[mi][nj][r]};
+                    if constexpr (RUNS) P[at] = cpx<T>{sr[mi][nj][r], si[mi][nj][r]};
                     else P[at] = cpx<T>{t1[mi][nj][r] + t2[mi][nj][r], t3[mi][nj][r] - t1[mi][nj][r] + t2[mi][nj][r]};
                 }
             }
@@ -754,27 +760,43 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(s
     }
 }
 
-// Splits of K.  Every workgroup of the launch is resident at once (two per CU;
-// complex64 products of 20 k-blocks a workgroup or more take three) and all have
-// the same number of k-blocks to within one (one tile, or two in complex64: one per CU, as the sum of
-// more partials costs more than it saves): a few workgroups past the last
-// whole round had cost most of a round (432 x 64 at K = 34208: 518 workgroups
-// 178 us, 511 117; 1001, in two rounds with twice the partials, 144).  Short
-// products stop at chunks of 5 k-blocks (8 for one tile, whose partials are
-// summed by few workgroups), then of 3 while that leaves CUs idle, then at 64
-// workgroups (256 x 23 at K = 11392: 44 splits 39.7 us, 128 30.6; 96 x 96 at
-// K = 3425: 14 splits 33 us, 64 21).  complex64 products of up to 16 runs of kRun
-// blocks have 16 chunks at least: their FP32 sums are as short as the chunks.
+// Splits of K.  Every workgroup of the launch is resident at once and all have the
+// same number of k-blocks to within one: a few workgroups past the last whole
+// round cost most of a round (432 x 64 at K = 34208: 518 workgroups 178 us, 511
+// 117).  One workgroup per CU until two have about six k-blocks each (complex64:
+// ten), three in complex64 from 20 on; the counts between leave some CUs with
+// twice the work of others (128 x 64 at K = 11401 FP64: 284 workgroups 33 us, 256
+// 26; 748 x 64 at K = 1900: 276 33, 252 26).  One tile, and two in complex64, stay
+// at one: more partials cost more than they save.  Chunks of three k-blocks at
+// least, but of one or two while those fill no more than half of the CUs (16 x 16
+// at K = 1200: 75 chunks 8.8 us, 64 uneven ones 9.5), of four for one tile in FP64
+// where they fill half (its partials are summed by few workgroups), and there no
+// more chunks than the longest of them needs.  complex64 products of up to 16
+// k-blocks keep a chunk for each: their FP32 sums are as short.
 // target > 0: a cap on the workgroups from the tuning, below these.
 int choose_split(int64_t K, int tiles, int target, bool cplx64, int cu) {
-    const int64_t nkb = (K + 15) / 16;
-    const int64_t built_in = tiles <= (cplx64 ? 2 : 1) ? cu : (cplx64 && nkb * tiles >= 20 * 3 * cu) ? 3 * cu : 2 * cu;
-    const int64_t cap = target > 0 ? target : 1024, slots = std::min(built_in, cap);
-    const int64_t longc = nkb / (tiles == 1 ? 8 : 5);
-    const int64_t mid = std::min<int64_t>(cu / tiles, nkb / 3);
-    const int64_t shortc = std::min<int64_t>(64 / tiles, nkb);
-    const int64_t least = cplx64 && nkb <= 16 * kRun ? std::min<int64_t>(cap / tiles, std::min<int64_t>(nkb, 16)) : 1;
-    return (int)std::max({(int64_t)1, least, std::min(slots / tiles, std::max({longc, mid, shortc}))});
+    const int64_t nkb = (K + 15) / 16, cap = target > 0 ? target : kTnSplitMax;
+    const int64_t half = cu / 2 / tiles, one = std::max(1, cu / tiles), two = 2 * cu / tiles, three = 3 * cu / tiles;
+    int64_t ns = std::min(one, (nkb + 2) / 3);
+    if (tiles == 1 && !cplx64) ns = std::min(ns, std::max(half, (nkb + 3) / 4));
+    if (2 * half >= nkb) ns = half >= nkb ? nkb : (nkb + 1) / 2;
+    if (tiles > (cplx64 ? 2 : 1) && 2 * nkb >= (cplx64 ? 20 : 11) * two) ns = two;
+    if (tiles > 2 && cplx64 && nkb >= 20 * three) ns = three;
+    if (cplx64 && nkb <= 16) ns = std::min(nkb, kTnSplitMax / (int64_t)tiles);
+    ns = std::max<int64_t>(1, std::min(ns, cap / tiles));
+    if (cplx64) return (int)ns;
+    const int64_t chunk = std::max<int64_t>(1, (nkb + ns - 1) / ns);
+    return (int)std::max<int64_t>(1, (nkb + chunk - 1) / chunk);
+}
+
+// k-blocks in one FP32 sum of complex64 chunks of up to `chunk`: kRun, fewer where K
+// is short (the error is to be no larger than that of 16 chunks) or where two
+// workgroups per CU, had they paid, would have had fewer; 0 if no chunk is longer
+int run_length(int64_t nkb, int tiles, int64_t chunk, int cu) {
+    const int64_t slots = (tiles > 2 ? 2 : 1) * cu;
+    const int64_t part = std::min((nkb + 15) / 16, std::max<int64_t>(3, (nkb * tiles + slots - 1) / slots));
+    if (chunk <= std::min<int64_t>(kRun, part)) return 0;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(kRun, part - 1));
 }
 
 }  // namespace
@@ -813,8 +835,17 @@ void gemm_tn_impl(const cpx<T> *A, int64_t lda, const cpx<T> *B, int64_t ldb, in
     // partials in the block type (the buffer is sized for complex128)
     cpx<T> *pt = reinterpret_cast<cpx<T> *>(part);
     const int64_t nkb = (K + 15) / 16;
-    hipLaunchKernelGGL((k_gemm_tn_lds<T, BF>), dim3(total), dim3(kThreads), 0, st, A, lda, B, ldb, K, p, q,
-                       tiles_m, tiles_n, ns, nkb / ns, (int)(nkb % ns), pt, herm ? 1 : 0);
+    auto tn = [&](auto runs, int run) {
+        hipLaunchKernelGGL((k_gemm_tn_lds<T, BF, decltype(runs)::value>), dim3(total), dim3(kThreads), 0, st, A, lda, B,
+                           ldb, K, p, q, tiles_m, tiles_n, ns, nkb / ns, (int)(nkb % ns), run, pt, herm ? 1 : 0);
+    };
+    const int run = run_length(nkb, ntile, (nkb + ns - 1) / ns, device_cu_count());
+    if constexpr (sizeof(T) == 4) {
+        if (run) tn(std::true_type{}, run);
+        else tn(std::false_type{}, 0);
+    } else {
+        tn(std::false_type{}, 0);
+    }
     const int64_t n = (int64_t)per_split;
     const unsigned rgroups = (unsigned)((n + 63) / 64);
     if (rgroups < 256)
