@@ -644,17 +644,21 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(s
 #pragma unroll
     for (int u = 0; u < 4; ++u) ra1[u] = cpx<T>{T(0), T(0)};
     cd rc[4];
+    // column 4 wave of the next whole k-block, carried along: computed for each block it
+    // delayed the loads by 60 ns (complex64 748 x 64 at K = 1900 47.6 us, 44.5 so)
+    const cpx<T> *Ak = A + (int64_t)(4 * wave) * lda + rbase;
     auto gload = [&](int kb) {
         if (near && kb + KB <= p) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                ra0[u] = at_offset(A + (int64_t)(kb + 4 * wave + u) * lda + rbase, va0);
+                ra0[u] = at_offset(Ak + u * lda, va0);
                 rc[u] = at_offset(Ct + kb, vc[u]);
             }
             if (upper) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) ra1[u] = at_offset(A + (int64_t)(kb + 4 * wave + u) * lda + rbase, va1);
+                for (int u = 0; u < 4; ++u) ra1[u] = at_offset(Ak + u * lda, va1);
             }
+            Ak += KB * lda;
         } else {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
