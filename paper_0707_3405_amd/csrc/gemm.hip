@@ -764,33 +764,38 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(s
     }
 }
 
-// Splits of K.  Every workgroup of the launch is resident at once and all have the
-// same number of k-blocks to within one: a few workgroups past the last whole
-// round cost most of a round (432 x 64 at K = 34208: 518 workgroups 178 us, 511
-// 117).  One workgroup per CU until two have about six k-blocks each (complex64:
-// ten), three in complex64 from 20 on; the counts between leave some CUs with
-// twice the work of others (128 x 64 at K = 11401 FP64: 284 workgroups 33 us, 256
-// 26; 748 x 64 at K = 1900: 276 33, 252 26).  One tile, and two in complex64, stay
-// at one: more partials cost more than they save.  Chunks of three k-blocks at
-// least, but of one or two while those fill no more than half of the CUs (16 x 16
-// at K = 1200: 75 chunks 8.8 us, 64 uneven ones 9.5), of four for one tile in FP64
-// where they fill half (its partials are summed by few workgroups), and there no
-// more chunks than the longest of them needs.  complex64 products of up to 16
-// k-blocks keep a chunk for each: their FP32 sums are as short.
+// Splits of K.  Every workgroup of the launch is resident at once: a few past the
+// last whole round cost most of a round (432 x 64 at K = 34208: 518 workgroups 178
+// us, 511 117).  One workgroup per CU until two have enough k-blocks each, as the
+// counts between leave some CUs with twice the work of others (128 x 64 at K = 11401
+// FP64: 284 workgroups 33 us, 256 26; 748 x 64 at K = 1900: 276 33, 252 26); three
+// in complex64.  What is enough grows with the part of a tile that there is to
+// compute (`quarters`): where it is little, the loads' latency is all of the time, and
+// more workgroups hide it (complex64 at K = 20000: 256 x 16 with one / two / three
+// per CU 27 / 21.3 / 20.7 us, 256 x 64 37 / 38.6 / -; FP64 432 x 8 at K = 5200 21.8
+// / 19.5, 432 x 64 34.1 / 34.4).  One tile, and two in complex64, need more: their
+// partials are summed by few workgroups.  Chunks of three k-blocks at least, but of
+// one or two while those fill no more than half of the CUs, or all where a tile has
+// little, but for one tile (164 x 6 at K = 700: 15 chunks 9.3 us, 44 8.4; 16 x 16 at
+// K = 1200: 75 even ones 8.8, 64 9.5), and of four for one tile in FP64 where they fill half.
+// complex64 products of up to 16 k-blocks keep a chunk for each: their FP32 sums are
+// as short.
 // target > 0: a cap on the workgroups from the tuning, below these.
-int choose_split(int64_t K, int tiles, int target, bool cplx64, int cu) {
+int choose_split(int64_t K, int p, int q, int tiles, int target, bool cplx64, int cu) {
     const int64_t nkb = (K + 15) / 16, cap = target > 0 ? target : kTnSplitMax;
-    const int64_t half = cu / 2 / tiles, one = std::max(1, cu / tiles), two = 2 * cu / tiles, three = 3 * cu / tiles;
+    const int64_t sub = (int64_t)((p + 15) / 16) * ((q + 15) / 16);   // 16 x 16 parts, 16 to a whole tile
+    const int quarters = (int)std::min<int64_t>(4, (sub + 4 * tiles - 1) / (4 * tiles));
+    const int64_t one = std::max(1, cu / tiles), two = 2 * cu / tiles, three = 3 * cu / tiles;
+    const int64_t few = (quarters > 2 || tiles == 1 ? cu / 2 : cu) / tiles;
     int64_t ns = std::min(one, (nkb + 2) / 3);
-    if (tiles == 1 && !cplx64) ns = std::min(ns, std::max(half, (nkb + 3) / 4));
-    if (2 * half >= nkb) ns = half >= nkb ? nkb : (nkb + 1) / 2;
-    if (tiles > (cplx64 ? 2 : 1) && 2 * nkb >= (cplx64 ? 20 : 11) * two) ns = two;
-    if (tiles > 2 && cplx64 && nkb >= 20 * three) ns = three;
+    if (tiles == 1 && !cplx64) ns = std::min(ns, std::max<int64_t>(cu / 2, (nkb + 3) / 4));
+    if (2 * few >= nkb) ns = few >= nkb ? nkb : (nkb + 1) / 2;
+    const double enough = cplx64 ? 2.5 * quarters * (tiles == 1 ? 4 : tiles == 2 ? 2 : 1)
+                                 : tiles == 1 ? 10.0 : std::min(5.5, 1.25 + 1.5 * quarters);
+    if (nkb >= enough * two && two > ns) ns = two;
+    if (cplx64 && tiles > 2 && nkb >= 5.0 * quarters * three) ns = three;
     if (cplx64 && nkb <= 16) ns = std::min(nkb, kTnSplitMax / (int64_t)tiles);
-    ns = std::max<int64_t>(1, std::min(ns, cap / tiles));
-    if (cplx64) return (int)ns;
-    const int64_t chunk = std::max<int64_t>(1, (nkb + ns - 1) / ns);
-    return (int)std::max<int64_t>(1, (nkb + chunk - 1) / chunk);
+    return (int)std::max<int64_t>(1, std::min({ns, nkb, cap / tiles}));
 }
 
 // k-blocks in one FP32 sum of complex64 chunks of up to `chunk`: kRun, fewer where K
@@ -809,11 +814,11 @@ size_t gemm_tn_part_elems(int64_t K, int p, int q, int *nsplit_out) {
     const int tiles_m = (p + kTile - 1) / kTile, tiles_n = (q + kTile - 1) / kTile;
     // for an MI355X: a host-only context has no device to ask, and more splits than fit
     // the partial buffer are never taken
-    auto most = [&](int tiles) { return std::max(choose_split(K, tiles, 0, false, 256), choose_split(K, tiles, 0, true, 256)); };
+    auto most = [&](int tiles) { return std::max(choose_split(K, p, q, tiles, 0, false, 256), choose_split(K, p, q, tiles, 0, true, 256)); };
     const int ns = most(tiles_m * tiles_n);
     if (nsplit_out) *nsplit_out = ns;
     size_t elems = (size_t)ns * p * q;
-    if (p == q) {   // the Hermitian form: whole tiles, on and above the diagonal
+    if (p == q && tiles_m >= 2) {   // the Hermitian form: whole tiles, on and above the diagonal
         const int nt = tiles_m * (tiles_m + 1) / 2;
         elems = std::max(elems, (size_t)most(nt) * nt * kTile * kTile);
     }
@@ -832,7 +837,7 @@ void gemm_tn_impl(const cpx<T> *A, int64_t lda, const cpx<T> *B, int64_t ldb, in
     herm = herm && p == q && tiles_m >= 2 && !scale_row && beta == 0.0;
     const int ntile = herm ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
     const size_t per_split = herm ? (size_t)ntile * kTile * kTile : (size_t)p * q;
-    int ns = choose_split(K, ntile, thread_tuning().tn_split_wgs, sizeof(T) == 4, device_cu_count());
+    int ns = choose_split(K, p, q, ntile, thread_tuning().tn_split_wgs, sizeof(T) == 4, device_cu_count());
     if ((size_t)ns * per_split > part_elems) ns = (int)(part_elems / per_split);
     PW_REQUIRE(ns >= 1, PW_ERR_NOMEM, "GEMM partial buffer too small");
     const int total = ntile * ns;
