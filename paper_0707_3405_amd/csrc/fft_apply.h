@@ -571,17 +571,17 @@ constexpr int kSticksPerBlock = 16;   // default sticks per workgroup of the z p
 // 272; N = 96, 61 columns 287 and 377; 2 x 6: N = 108, 53 columns 405 and 447).
 // With one workgroup up to 12 waves (N = 120, FP32: 2 x 4 458, 1 x 12 402), but
 // for R2 = 16, whose items collide in the banks whatever the waves (N = 128, FP32:
-// 533 and 558).  With no more planes than compute units nothing else runs beside
+// 533 and 558).  few: no more planes than compute units, so nothing else runs beside
 // a workgroup, and up to 12 waves shorten it (one band, 12 / 4 waves: N = 72 FP64
 // 23.2 / 27.0 us, N = 80 26.4 / 30.6, N = 96 FP32 23.5 / 30.0).
 // most > 0: a cap from the tuning, below these.  0 if even one wave does not fit.
 template <class P, class T>
-int plane_waves(int ncx, int most, int64_t planes) {
+int plane_waves(int ncx, int most, bool few) {
     using W = PlaneWave<P>;
     constexpr bool F32 = sizeof(T) == 4 && P::R2 != 16;
     auto lds = [&](int nw) { return plane_columns<P, T>(ncx) + nw * W::xbytes(); };
     int nw = kPlaneWaves;
-    if (planes > device_cu_count()) {
+    if (!few) {
         if (lds(4) * (!F32 ? 2 : P::N <= 96 ? 4 : 3) <= kLdsMax) nw = 4;
         else if (F32 && lds(6) * 2 <= kLdsMax) nw = lds(8) * 2 <= kLdsMax ? 8 : 6;
     }
@@ -615,7 +615,7 @@ void run_apply_split(const ApplyItems<T> &items, int nk, const T *vperm, int nb,
                 ncx_max = std::max(ncx_max, items.it[k].sp.ncx);
             }
         if (!n) return;
-        const int nw = plane_waves<P, T>(ncx_max, most, (int64_t)N * nb * n);
+        const int nw = plane_waves<P, T>(ncx_max, most, (int64_t)N * nb * n <= device_cu_count());
         PW_REQUIRE(nw >= 1, PW_ERR_ARG, "FFT plane does not fit in LDS");
         const size_t sm2 = plane_columns<P, T>(ncx_max) + nw * W::xbytes();
         if (!launch) return ensure_smem_limit((const void *)k_plane<P, T, H>, sm2);

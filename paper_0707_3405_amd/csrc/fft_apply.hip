@@ -212,7 +212,7 @@ struct DensityShape {
     using W = PlaneWave<P>;
     static size_t lds(int ncx, int nw) { return plane_columns<P, double>(ncx) + nw * W::xbytes(); }
     static bool reg(int ncx) { return W::NG <= kPlaneWaves && lds(ncx, W::NG) <= kLdsMax; }
-    static int waves(int ncx) { return reg(ncx) ? W::NG : plane_waves<P, double>(ncx, 0, INT64_MAX); }
+    static int waves(int ncx) { return reg(ncx) ? W::NG : plane_waves<P, double>(ncx, 0, false); }
 };
 
 template <int N>

@@ -300,8 +300,9 @@ size_t density_bytes(const pw_ctx_s &c, int chunk, int nb) {
 // all, if fewer): neither the workspace nor its block size enters, as the groups
 // fix the order of the sum.
 constexpr int kDensityBands = 64;
-int density_groups(int n, int resident, int nb) {
-    const int slots = pw::device_cu_count() * std::max(1, resident), nc = std::min(nb, kDensityBands);
+int density_groups(const pw_ctx_s &c, int nb) {
+    const int n = c.n, resident = pw::density_resident(c.sp), cu = c.device >= 0 ? pw::device_cu_count() : 256;
+    const int slots = cu * std::max(1, resident), nc = std::min(nb, kDensityBands);
     int best = 1;
     double cost = HUGE_VAL;
     for (int g = 1; g <= nc; ++g) {
@@ -314,11 +315,14 @@ int density_groups(int n, int resident, int nb) {
     return best;
 }
 
-// the solver's plan, and enough for pw_density of up to M bands with the same block
+// the solver's plan, and room for pw_density of up to M bands with the same block, the
+// groups side by side
 size_t plan_bytes(const pw_ctx_s &c, int M, int m, pw_precision prec) {
     size_t b = make_plan<cd>(c, M, m, nullptr).bytes;
     if (prec != PW_PREC_FP64) b = std::max(b, make_plan<pw::cf>(c, M, m, nullptr).bytes);
-    return std::max(b, density_bytes(c, m, M));
+    int groups = 1;
+    for (int nb = 2; nb <= std::min(M, kDensityBands); ++nb) groups = std::max(groups, density_groups(c, nb));
+    return std::max(b, density_bytes(c, m, M) + (size_t)(groups - 1) * c.n * c.n * c.n * sizeof(double));
 }
 
 void require_precision(pw_precision prec) {
@@ -1612,7 +1616,7 @@ pw_status pw_density(pw_ctx c, const void *X, int64_t ldx, int32_t nb, const dou
                                        m[2] * (m[3] * m[7] - m[4] * m[6]));
         // every group's sum at once where the workspace holds them, else one group after
         // the other through one grid: the same additions in the same order
-        const int groups = density_groups(c->n, pw::density_resident(c->sp), nb);
+        const int groups = density_groups(*c, nb);
         const size_t room = (c->ws_bytes - align_up(a.used, 256)) / (n3 * 8);   // >= 1 by the check above
         const int at_once = room >= (size_t)groups ? groups : 1, rounds = groups / at_once;
         double *part = a.take<double>((size_t)n3 * at_once);
