@@ -218,10 +218,11 @@ typedef struct {
 /* Autotuner for this context's shapes (batched k-points and served requests
  * differ in npw, grid and projector count): times the local H X of nb bands
  * (1 <= nb <= block of the workspace) for every radix split of the grid's FFT
- * length x sticks per block {16, 32, 64} x plane rows {16, 32, 48, 96}, and the Rayleigh-Ritz Gram (3 block x 3 block over
- * npw) plus the projector overlaps with and without a split cap of 384,
- * with HIP events on the context stream (mean of 5 after a warm-up); keeps
- * the fastest of each (or the default when nothing beats it) for later
+ * length x sticks per block {16, 32, 64} x plane rows {16, 32, 48, 96}, and the
+ * Rayleigh-Ritz Gram (3 block x 3 block over npw) plus the projector overlaps
+ * with and without a split cap of 384, with HIP events on the context stream
+ * (mean of 5 after a warm-up; the default before and after the others); keeps
+ * the fastest of each (or the default when nothing beats it by 1 %) for later
  * calls on this context and reports it in *out.  Needs basis, potential,
  * projectors if any, and a workspace; overwrites workspace contents only.
  * Synchronises the stream. */
