@@ -1,12 +1,14 @@
-// Small dense FP64 steps of the iteration, each in one workgroup.
+// Small dense FP64 steps of the iteration.
 //
-//  * k_chol_inv: Cholesky factor of a Gram matrix G = R^H R and R^-1, used to
-//    orthonormalise a block (W <- W R^-1; BLOPEX-style LOBPCG, sec. 3.2).
-//  * k_heev: lowest k eigenpairs of a Hermitian matrix -- the Rayleigh-Ritz
+//  * k_chol_inv (one workgroup): Cholesky factor of a Gram matrix G = R^H R and
+//    R^-1, used to orthonormalise a block (W <- W R^-1; BLOPEX-style LOBPCG, sec. 3.2).
+//  * launch_heev_f64: lowest k eigenpairs of a Hermitian matrix -- the Rayleigh-Ritz
 //    eigenproblem of the LOBPCG iteration (sec. 3.2, Algorithm 1; size 3m) and of the final
 //    Rayleigh-Ritz over all bands (sec. 3.2, sec. 4.2).  Householder
-//    reduction to real tridiagonal form, bisection with Sturm counts,
-//    inverse iteration, classical Gram-Schmidt applied twice, back-transform.
+//    reduction to real tridiagonal form (many workgroups down to 96 rows, then
+//    one), bisection with Sturm counts (a workgroup per eigenvalue), inverse
+//    iteration (a wave per eigenvalue), re-orthogonalisation (CholQR or Gram-Schmidt
+//    twice), back-transform (a wave per vector).
 #include <algorithm>
 #include <cfloat>
 #include <cmath>
@@ -885,7 +887,7 @@ __device__ int sturm_minors(const double2 *de, int n, double x, bool &lost) {
 // there, so one point per thread and one wave per SIMD (more points per round
 // save fewer rounds than their issue slots cost).  Lowest 64 of n = 192:
 // 133 us with the ratio form at 512 points, 36 us with the minors; all of
-// n = 512: 532 -> 117 us us.
+// n = 512: 532 -> 117 us.
 // rel_tol: relative width at which a bracket stops (DBL_EPSILON; FLT_EPSILON
 // for a tridiagonal matrix from the FP32 reduction, whose eigenvalues carry
 // FP32 rounding anyway).
@@ -1136,8 +1138,9 @@ __global__ void __launch_bounds__(1024) k_orth(double *__restrict__ Zg, int n, i
 // backward error of the inverse-iteration solves over the gap, and unit).  One
 // workgroup per column, the one of a cluster's first column takes the whole
 // cluster and the others leave, so clusters run side by side and a column
-// on its own costs nothing (all of n = 512, no clusters: 2066 us as one workgroup over every
-// column, 9 us so).
+// on its own costs nothing and is left as the inverse iteration made it, a unit
+// vector (all of n = 512, no clusters: 2066 us as one workgroup over every column,
+// 6.2 us so).
 __global__ void __launch_bounds__(1024) k_orth_clusters(double *__restrict__ Z, int n, int k,
                                                         const double *__restrict__ w, double ctol_rel,
                                                         const double *__restrict__ dd,

@@ -460,6 +460,10 @@ struct PlaneLane {
 // writes (8 bytes a lane at best 85 B per cycle; reads run at 256).  Against the
 // form with a barrier after each of ~14 stages, 64 bands: N = 96 413 -> 307 us
 // FP64, 198 -> 176 FP32; N = 72, 92 bands, 290 -> 172 FP64.
+// The bound of 12 waves holds every instance to 168 VGPRs, those launched with four
+// waves too: in FP64 the default splits spill 28 of them (100 bytes of scratch a
+// lane) at N = 120, 22 at 128, 8 at 108 and, unpruned, 13 at 96; the density's
+// register form 9 at 96, 35 at 120 and 53 at 128.
 template <class P, class T, bool HALF>
 __global__ void __launch_bounds__(64 * kPlaneWaves) k_plane(const ApplyItems<T> items, const T *__restrict__ vperm,
                                                             int nb) {

@@ -602,7 +602,7 @@ __global__ void __launch_bounds__(kThreads)
 // stages the next one: of the waves on a SIMD the furthest finishes first and
 // loads while the others multiply, instead of all of them waiting in step.
 // K = 34208: complex64 432 x 64 82 -> 73 us, 192 x 64 41 -> 37, FP64 432 x 64
-// 129 -> 126, 64 x 64 26.4 -> 27.1; 82592: complex64 748 x 64 303 -> 272, FP64
+// 129 -> 126, 64 x 64 26.4 -> 25.7; 82592: complex64 748 x 64 303 -> 272, FP64
 // 494 -> 484; K = 11392: complex64 256 x 23 26.4 -> 23.2.  (Nothing is loaded past the
 // last block: 0.4 us of a call with few blocks.)  (k_gemm_tn_lds
 // measured 3-6 % slower with such loads, and 3-14 % with the priorities.)
